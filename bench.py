@@ -40,7 +40,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
 KERNEL_SOURCES = {
-    "dos_forward_kernel": ("tetra_forward.hip", "tetra_device.h", "tetra_internal.h", "tetra_weights.h"),
+    "dos_forward_kernel": ("tetra_forward.hip", "tetra_forward_args.h", "tetra_forward_kernels.h", "tetra_spline.h",
+                           "tetra_device.h", "tetra_internal.h", "tetra_weights.h"),
     # the adjoint pass: dos_backward_kernel and its gather pass, both in tetra_backward.hip
     "dos_backward_kernel": ("tetra_backward.hip", "tetra_device.h", "tetra_faces.h", "tetra_internal.h",
                             "tetra_weights.h"),

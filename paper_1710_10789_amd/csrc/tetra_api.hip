@@ -258,7 +258,7 @@ tetra_status tetra_dos_batched(const tetra_item* items, int n, int wtype, unsign
   if (!workspace || ws_bytes < 256 * tetra::batched_launches(items, n)) return TETRA_ERR_WORKSPACE;
   std::vector<int> shapes(n);
   for (int i = 0; i < n; ++i) shapes[i] = items[i].tile;
-  return hip_status(tetra::batched(items, shapes.data(), n, wtype, workspace, (hipStream_t)stream));
+  return hip_status(tetra::batched(items, shapes.data(), n, wtype, (hipStream_t)stream));
 }
 
 const char* tetra_status_string(int status) {

@@ -8,10 +8,11 @@
 
 namespace tetra {
 
-constexpr int kMaxBatch = 32;  // problems per persistent batched launch
+constexpr int kMaxBatch = 32;  // problems per batched launch
 
-// Tile shapes (cubes along grid axes 1, 2, 3) of the forward and adjoint kernels: one lane per cube,
-// kTileCubes lanes per workgroup. Shape 0 is the default; the others are for the autotuner.
+// Tile shapes (cubes along grid axes 1, 2, 3): one lane per cube, kTileCubes lanes per workgroup. Shape 0 is
+// the default; the others are for the autotuner. (The forward takes tiles of 8 x 8 x 8 cubes for shape 0
+// and each side up to 8 of the others.)
 constexpr int kTileCubes = 256;
 constexpr int kTileShapes = 6;
 struct TileShape {
@@ -31,10 +32,10 @@ hipError_t fill_zero(float* p, int64_t n, hipStream_t s);
 // forward_exact_scratch_bytes(d) for the exact cross-workgroup accumulation.
 hipError_t forward(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
                    void* exact_scratch, int shape, hipStream_t s);
-// Batched forward: items grouped by orbital count, up to kMaxBatch per persistent launch. The
-// workspace holds one 256-byte work counter per launch.
+// Batched forward: items grouped by orbital count, up to kMaxBatch per launch (the ABI asks for 256 bytes
+// of workspace per launch; the kernels use none).
 size_t batched_launches(const tetra_item* items, int n);
-hipError_t batched(const tetra_item* items, const int* shapes, int n, int wtype, void* workspace, hipStream_t s);
+hipError_t batched(const tetra_item* items, const int* shapes, int n, int wtype, hipStream_t s);
 // Exact mode of the forward: 256 bytes (the largest bound exponent), then ne*norb 64-bit sums.
 inline size_t forward_exact_scratch_bytes(const tetra_desc& d) { return 256 + 8 * (size_t)d.ne * d.norb; }
 // FP16 weights with a per-band power-of-two scale: w [nb][per_band] -> w16, w_scale [nb].
