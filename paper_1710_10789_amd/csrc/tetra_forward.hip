@@ -22,6 +22,7 @@ __global__ void exact_init_kernel(int* gexp, unsigned long long* acc, int64_t n)
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     acc[i] = 0ull;
 }
+}  // namespace
 
 constexpr int kSide = 8;  // largest tile side, in cubes
 
@@ -46,6 +47,10 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
   a.V = (float)V;
   a.inv_ded = 1.0 / (double)d.de;
   a.c4 = 4.0 * V * a.inv_ded;
+  a.joff = 0.0;
+  a.Vd = V;
+  a.out_scale = 1.0;
+  a.shift = 0;
   const TileShape sh = tile_shape(shape);
   const int side[3] = {shape ? std::min(sh.x, kSide) : kSide, shape ? std::min(sh.y, kSide) : kSide,
                        shape ? std::min(sh.z, kSide) : kSide};
@@ -76,8 +81,6 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
   while ((1ll << a.lg_units) < (long long)a.nunits) ++a.lg_units;
   return a;
 }
-
-}  // namespace
 
 hipError_t fill_zero(float* p, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;

@@ -37,6 +37,10 @@ struct FwdArgs {
   FastDiv by_ntiles, by_t2, by_t3;
   int ntiles, nunits, per_xcd;
   int lanes;  // workgroup size: a lane per cube of the largest tile, in whole waves
+  // number of states: grid index j stands for e0 + (j + joff) de and goes to output row j - shift (rows below
+  // 0 are dropped), times out_scale; Vd = V_T/(4 V_G)
+  double joff, Vd, out_scale;
+  int shift;
 };
 
 // Problems of a batched launch (items in order, units band-major): what differs between them, small
@@ -62,10 +66,16 @@ struct BatchArgs {
 };
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments");
 
+// The arguments that do not depend on the kind of sum (shape: TETRA_TILE_* index).
+FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
+                     int shape);
+
 // Defined per orbital count in tetra_forward_inst*.hip.
 template <int NORB>
 hipError_t launch_fwd(const FwdArgs& a, int grid, hipStream_t s);
 template <int NORB>
 hipError_t launch_batched(const BatchArgs& b, int wtype, hipStream_t s);
+template <int NORB>
+hipError_t launch_nos(const FwdArgs& a, int grid, hipStream_t s);
 
 }  // namespace tetra

@@ -40,6 +40,7 @@
 
 #include "tetra_device.h"
 #include "tetra_forward_args.h"
+#include "tetra_nos_device.h"
 #include "tetra_spline.h"
 #include "tetra_weights.h"
 
@@ -518,9 +519,14 @@ union FwdShared {
 // The unit by the spline form; false (uniform across the workgroup) when the tile-band is not for it.
 // MODE 0: FP64 sums, flushed with float atomics. MODE 2: 64-bit integers, so that nothing depends on the
 // order of the atomics: a first sweep over the points finds the largest entry, which fixes the scale.
+// MODE 3: the increments N(E_j) - N(E_{j-1}) of the number of states on the grid e0 + (j + joff) de
+// (everything below the grid at index 0) instead of the DOS: fifth differences of quartics, and the same
+// four running sums.
 template <int NORB, typename WT, int MODE>
 __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineShared<NORB>& sh) {
   using Acc = typename std::conditional<MODE == 2, long long, double>::type;
+  constexpr bool INC = MODE == 3;
+  constexpr int NE = INC ? 5 : 4;  // entries of a point
   int band;
   const Tile tl = unit_tile(a, unit, band);
   const int x0 = tl.x0, y0 = tl.y0, z0 = tl.z0, cy = tl.cy, cz = tl.cz;
@@ -531,7 +537,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   const float* eps_n = a.eps + (int64_t)band * nk;
   const WT* w_n = static_cast<const WT*>(a.w) + (int64_t)band * NORB * nk;
   const float wscale = a.w_scale ? a.w_scale[band] : 1.0f;
-  const double e0 = a.e0, inv_de = a.inv_ded;
+  const double e0 = a.e0, inv_de = a.inv_ded, joff = INC ? a.joff : 0.0;
   if (nk >= (1ll << 29)) return false;  // byte offsets within a plane are 32-bit below
   auto split = [&](int q, int& px, int& py, int& pz) {
     const int r = small_div(q, by_qz);
@@ -559,7 +565,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     const bool finite = __builtin_isfinite(e);
     sh.f[p] = finite ? (e - first) * a.inv_de : __builtin_huge_valf();
     if (finite) {
-      sh.u[kKnotMargin + px * SY + py * SZ + pz] = ((double)e - e0) * inv_de;
+      sh.u[kKnotMargin + px * SY + py * SZ + pz] = ((double)e - e0) * inv_de - joff;
       lmin = fminf(lmin, e);
       lmax = fmaxf(lmax, e);
     }
@@ -590,12 +596,43 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   emin = uniform(emin);
   emax = uniform(emax);
   if (!(emin <= emax)) return true;  // no finite energy
-  const double umin = ((double)emin - e0) * inv_de, umax = ((double)emax - e0) * inv_de;
-  if (!(umax > 0.0) || !(umin < (double)(a.ne - 1))) return true;  // outside the energy grid
+  const double umin = ((double)emin - e0) * inv_de - joff, umax = ((double)emax - e0) * inv_de - joff;
+  if (!(umin < (double)(a.ne - 1))) return true;  // above the energy grid
+  if (!(uniform(bmax) < 3.0e38f)) return false;
+  if (!(umax > 0.0)) {  // below it
+    if (INC && a.shift == 0) {
+      // every state counts at index 0: each finite tetrahedron gives V times its corners' weights
+      for_lanes(NORB, [&](int m) { sh.hist[m] = 0.0; });
+      __syncthreads();
+      for (int m = 0; m < NORB; ++m) {
+        double sum = 0.0;
+        for_lanes(ncubes, [&](int c) {
+          const int r = c / cz, iz = c - r * cz, ix = r / cy, iy = r - ix * cy, p = ix * PY + iy * PZ + iz;
+#pragma unroll
+          for (int t = 0; t < 6; ++t) {
+            const uint32_t slots = tet_slots(t);
+            float top = -__builtin_huge_valf(), b = 0.0f;
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+              const int s = (slots >> (4 * l)) & 7, q = p + (s & 1) * PY + ((s >> 1) & 1) * PZ + (s >> 2);
+              top = fmaxf(top, sh.f[q]);
+              b += sh.w[m * NP + q];
+            }
+            sum += top < __builtin_huge_valf() ? (double)b : 0.0;
+          }
+        });
+        if (sum != 0.0) unsafeAtomicAdd(&sh.hist[m], sum);
+      }
+      __syncthreads();
+      for_lanes(NORB, [&](int m) { atomic_add_global(&a.dos[m], (float)(sh.hist[m] * a.Vd)); });
+    }
+    return true;
+  }
   // Rows of the sums: from the first grid energy at or above the lowest knot (below the grid's first
-  // energy too) to the last one below the highest.
-  const double rows_d = fmin(ceil(umax), (double)a.ne) - floor(umin);
-  if (!(uniform(bmax) < 3.0e38f) || !(rows_d + 6.0 <= (double)spline_words<NORB>())) return false;
+  // energy too) to the last one below the highest (the first at or above it for the increments).
+  const double rows_d = INC ? fmin(ceil(umax), (double)(a.ne - 1)) + 1.0 - floor(umin)
+                            : fmin(ceil(umax), (double)a.ne) - floor(umin);
+  if (!(rows_d + NE + 2 <= (double)spline_words<NORB>())) return false;
   const int base = uniform((int)floor(umin)), rows = uniform((int)rows_d);
   const float J = (float)rows, limit = (MODE == 2 ? kDegenerateExact : kDegenerate) * J * J * J;
 
@@ -635,13 +672,13 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
 
   // As many orbitals at a time as the histogram holds, then as many copies of it (a lane adds into copy
   // lane mod copies: neighbouring points often share a bin).
-  const int RS = (rows + 5) | 1;
+  const int RS = (rows + NE + 1) | 1;
   int group = NORB;
   while (RS * group > spline_words<NORB>()) group = (group + 1) / 2;
   const int plane = RS * group;
   const int copies = 4 * plane <= spline_words<NORB>() ? 4 : 2 * plane <= spline_words<NORB>() ? 2 : 1;
   Acc* const hist = reinterpret_cast<Acc*>(sh.hist);
-  const double c4 = a.c4;
+  const double c4 = INC ? a.Vd : a.c4;
 
   // Coefficients of this lane's point q, then act(m, D) with the four entries of every orbital of the
   // group [m0, m1), scaled by `scale`.
@@ -670,12 +707,13 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     double Ms = 0.0;
 #pragma unroll
     for (int u = 0; u < kNeighbours; ++u) Ms += M[u];
-    double N[4], n[4];
-    knot_differences(ju - u0, N, n);
+    double N[NE], n[NE];
+    if constexpr (INC) knot_differences(ju - u0, N, n, true);
+    else knot_differences(ju - u0, N, n);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NE; ++i) {
       N[i] *= scale;
-      n[i] *= scale * T;
+      n[i] *= scale * (INC ? (4.0 / 3.0) * T : T);
     }
     const int row = (int)(ju - base);
     auto orbital = [&](int m) {
@@ -690,9 +728,9 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
         q = __builtin_fma(M[u], (double)w[dx * PY + dy * PZ + dz], q);
       }
       Q += Q1;
-      double D[4];
+      double D[NE];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) D[i] = __builtin_fma(Q, N[i], bp * n[i]);
+      for (int i = 0; i < NE; ++i) D[i] = __builtin_fma(Q, N[i], bp * n[i]);
       act(m - m0, row, D);
     };
 #pragma unroll 1
@@ -717,30 +755,46 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       pt[l] = px * PY + py * PZ + pz;
     }
     sort4(e, pt);
-    if (!(e[3] > e[0])) return;
-    int jlo, jhi;
-    energy_window(e[0], e[3], a.e0, a.inv_de, 0, a.ne - 1, jlo, jhi);
-    const TetSetup cs = tet_setup(e, a.e0, a.V);
-    tet_window(cs, a.de, 0, a.ne - 1, jlo, jhi);
-    int jA, jB;
-    case_split(cs, a.de, a.inv_de, jlo, jhi, jA, jB);
-    float coef[4][4];
-    if (jB > jA) corner_dos_B_coeffs(cs, a.V, coef);
-    for (int j = jlo + (i16 & 15); j <= jhi; j += 16) {
-      float g[4];
-      if (j <= jA) corner_dos_A(cs, local_x(cs, j, a.de), g);
-      else if (j <= jB) corner_dos_B_poly(coef, local_z(cs, j, a.de), g);
-      else corner_dos_C(cs, local_y(cs, j, a.de), g);
+    if (!INC && !(e[3] > e[0])) return;
+    auto put = [&](int j, double g0, double g1, double g2, double g3) {
 #pragma unroll 1
       for (int m = m0; m < m1; ++m) {
         const float* w = sh.w + m * NP;
-        const double v = unit * (double)(g[0] * w[pt[0]] + g[1] * w[pt[1]] + g[2] * w[pt[2]] + g[3] * w[pt[3]]);
+        const double v = unit * (g0 * w[pt[0]] + g1 * w[pt[1]] + g2 * w[pt[2]] + g3 * w[pt[3]]);
         Acc* h = &hist[(m - m0) * RS + j - base];
         add(h, v, 1);
         add(h + 1, v, -4);
         add(h + 2, v, 6);
         add(h + 3, v, -4);
         add(h + 4, v, 1);
+      }
+    };
+    if constexpr (INC) {
+      const NosVolumes c = nos_volumes(e);
+      const double u1 = (c.e[0] - e0) * inv_de - joff, u4 = (c.e[3] - e0) * inv_de - joff;
+      const int js = (int)fmin(ceil(u4), (double)(base + rows - 1)), ja = min((int)floor(u1) + 1, js);
+      for (int j = ja + (i16 & 15); j <= js; j += 16) {
+        const double E = e0 + (j + joff) * (double)a.de;
+        double w0[4], w1[4];
+        corner_nos(c, 1.0, E - (double)a.de, w0);
+        corner_nos(c, 1.0, E, w1);
+        put(j, w1[0] - w0[0], w1[1] - w0[1], w1[2] - w0[2], w1[3] - w0[3]);
+      }
+    } else {
+      int jlo, jhi;
+      energy_window(e[0], e[3], a.e0, a.inv_de, 0, a.ne - 1, jlo, jhi);
+      const TetSetup cs = tet_setup(e, a.e0, a.V);
+      tet_window(cs, a.de, 0, a.ne - 1, jlo, jhi);
+      int jA, jB;
+      case_split(cs, a.de, a.inv_de, jlo, jhi, jA, jB);
+      float coef[4][4];
+      if (jB > jA) corner_dos_B_coeffs(cs, a.V, coef);
+      for (int j = jlo + (i16 & 15); j <= jhi; j += 16) {
+        float g[4];
+        if (j <= jA) corner_dos_A(cs, local_x(cs, j, a.de), g);
+        else if (j <= jB) corner_dos_B_poly(coef, local_z(cs, j, a.de), g);
+        else corner_dos_C(cs, local_y(cs, j, a.de), g);
+        put(j, g[0], g[1], g[2], g[3]);
       }
     }
   };
@@ -770,10 +824,10 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     const double scale = MODE == 2 ? uniform(ldexp(c4, sexp)) : c4;
     for_lanes(np, [&](int q) {
       Acc* const mine = hist + (q & (copies - 1)) * plane;
-      point(q, m0, m1, scale, [&](int m, int row, const double D[4]) {
+      point(q, m0, m1, scale, [&](int m, int row, const double D[NE]) {
         Acc* h = &mine[m * RS + row];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NE; ++i) {
           if constexpr (MODE == 2) {
             constexpr double magic = 6755399441055744.0;  // 1.5 * 2^52: the sum's low bits are the rounded value
             const long long v = __double_as_longlong(D[i] + magic) - __double_as_longlong(magic);
@@ -785,7 +839,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       });
     });
     for_lanes(16 * nq, [&](int i16) {
-      degenerate(i16, m0, m1, MODE == 2 ? ldexp(1.0, sexp) : 1.0, [&](Acc* h, double v, int times) {
+      degenerate(i16, m0, m1, MODE == 2 ? ldexp(1.0, sexp) : INC ? a.Vd : 1.0, [&](Acc* h, double v, int times) {
         if constexpr (MODE == 2)
           atomicAdd(reinterpret_cast<unsigned long long*>(h), (unsigned long long)(times * (long long)rint(v)));
         else
@@ -822,6 +876,13 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     }
     __syncthreads();
     const int lo = max(-base, 0);
+    if (INC && lo > 0 && a.shift == 0) {  // increments below the grid count at its first energy
+      for_lanes(lo * gm, [&](int i) {
+        const int m = i / lo;
+        unsafeAtomicAdd(&sh.hist[m * RS + lo], sh.hist[m * RS + i - m * lo]);
+      });
+      __syncthreads();
+    }
     for_lanes((rows - lo) * gm, [&](int i) {
       const int q = gm == NORB ? i / NORB : i / gm, r = lo + q, m = i - q * gm;
       const Acc v = hist[m * RS + r];
@@ -833,6 +894,9 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
         else if (dshift > -63) fixed = (v + (1ll << (-dshift - 1))) >> (-dshift);
         else fixed = 0;
         if (fixed != 0) atomicAdd(&a.gacc[at], (unsigned long long)fixed);
+      } else if constexpr (INC) {
+        if (v != 0.0 && base + r >= a.shift)
+          atomic_add_global(&a.dos[at - a.shift * NORB], (float)(v * a.out_scale));
       } else {
         if (v != 0.0) atomic_add_global(&a.dos[at], (float)v);
       }

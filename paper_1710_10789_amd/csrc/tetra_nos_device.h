@@ -66,6 +66,55 @@ __host__ __device__ __forceinline__ void corner_nos_C(const TetSetup& c, float V
   w[3] = V - t * (4.0f - y * c.sC);
 }
 
+// The integrated weights by volumes, in FP64 from the sorted corner energies and six reciprocals (few
+// registers, no cancellation): the part below E of a tetrahedron is one tetrahedron in the first case,
+// three in the middle one, the whole less one in the third, and each of those carries a quarter of its
+// volume per vertex, shared out by the vertex's barycentric coordinates. V = V_T/(4 V_G).
+struct NosVolumes {
+  double e[4];
+  double r21, r31, r41, r32, r42, r43;
+};
+__host__ __device__ __forceinline__ NosVolumes nos_volumes(const float e[4]) {
+  NosVolumes c;
+  for (int l = 0; l < 4; ++l) c.e[l] = e[l];
+  // Reciprocals of zero differences are infinite; the case that would use them is never selected.
+  c.r21 = 1.0 / (c.e[1] - c.e[0]);
+  c.r31 = 1.0 / (c.e[2] - c.e[0]);
+  c.r41 = 1.0 / (c.e[3] - c.e[0]);
+  c.r32 = 1.0 / (c.e[2] - c.e[1]);
+  c.r42 = 1.0 / (c.e[3] - c.e[1]);
+  c.r43 = 1.0 / (c.e[3] - c.e[2]);
+  return c;
+}
+__host__ __device__ __forceinline__ void corner_nos(const NosVolumes& c, double V, double E, double w[4]) {
+  const double x = E - c.e[0], y = c.e[3] - E;
+  if (!(y > 0.0)) {
+    w[0] = w[1] = w[2] = w[3] = V;
+  } else if (!(x > 0.0)) {
+    w[0] = w[1] = w[2] = w[3] = 0.0;
+  } else if (E <= c.e[1]) {
+    const double a = x * c.r21, b = x * c.r31, d = x * c.r41, f = V * a * b * d;
+    w[0] = f * (4.0 - a - b - d);
+    w[1] = f * a;
+    w[2] = f * b;
+    w[3] = f * d;
+  } else if (E <= c.e[2]) {
+    const double z = E - c.e[1], r13 = x * c.r31, r14 = x * c.r41, r23 = z * c.r32, r24 = z * c.r42;
+    const double s23 = 1.0 - r23, s24 = 1.0 - r24;
+    const double a = V * r13 * r14 * s24, b = V * r13 * r24 * s23, d = V * r23 * r24;
+    w[0] = a * (3.0 - r13 - r14) + b * (2.0 - r13) + d;
+    w[1] = a * s24 + b * (s24 + s23) + d * (1.0 + s23 + s24);
+    w[2] = a * r13 + b * (r13 + r23) + d * r23;
+    w[3] = a * (r14 + r24) + b * r24 + d * r24;
+  } else {
+    const double a = y * c.r41, b = y * c.r42, d = y * c.r43, f = V * a * b * d;
+    w[0] = V - f * a;
+    w[1] = V - f * b;
+    w[2] = V - f * d;
+    w[3] = V - f * (4.0 - a - b - d);
+  }
+}
+
 // FP64 constants of one tetrahedron-band.
 struct NosSetup {
   double x0, z0, y0;  // grid index 0 in the local frames: E_0 - E1, E_0 - E2, E4 - E_0

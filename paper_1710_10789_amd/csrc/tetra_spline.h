@@ -144,4 +144,24 @@ __host__ __device__ __forceinline__ void knot_differences(double x, double N[4],
   n[3] = -y2;
 }
 
+// The same for the integrated weights (number of states): a tetrahedron's number of states is the quartic
+//     V sum_p [ (4/3) T b_p (E - E_p)_+^3 + sum_u M_u (b_u - b_p) (E - E_p)_+^4 ],
+// and N[i], n[i] the fifth differences of x_+^4 and x_+^3.
+__host__ __device__ __forceinline__ void knot_differences(double x, double N[5], double n[5], bool) {
+  double N3[4], n2[4];
+  knot_differences(x, N3, n2);
+  const double y = 1.0 - x, x2 = x * x, y2 = y * y, p = x2 * x2, q = y2 * y2;
+  const double xp = 1.0 + x, yp = 1.0 + y, xp2 = xp * xp, yp2 = yp * yp;
+  N[0] = p;
+  N[1] = __builtin_fma(-5.0, p, xp2 * xp2);
+  N[3] = __builtin_fma(-5.0, q, yp2 * yp2);
+  N[4] = q;
+  N[2] = 24.0 - ((N[0] + N[1]) + (N[3] + N[4]));
+  n[0] = N3[0];
+  n[1] = N3[1] - N3[0];
+  n[2] = N3[2] - N3[1];
+  n[3] = N3[3] - N3[2];
+  n[4] = -N3[3];
+}
+
 }  // namespace tetra

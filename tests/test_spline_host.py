@@ -31,4 +31,5 @@ def test_spline_form_against_the_oracle(tmp_path, oracle_lib):
     rows = {line.split()[0]: line.split()[1:] for line in out.stdout.strip().split("\n")}
     blocks, left, err = int(rows["block"][0]), int(rows["block"][1]), float(rows["block"][2])
     assert blocks == 60 and left > 100 and err <= 2e-5
+    assert float(rows["states"][0]) <= 2e-5
     assert int(rows["division"][0]) == 0
