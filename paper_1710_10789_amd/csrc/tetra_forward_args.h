@@ -30,6 +30,7 @@ struct FwdArgs {
   int wtype;                 // TETRA_W_* of w
   int n1, n2, n3, ne;
   float e0, de, inv_de, V;
+  float degenerate;    // limit of a degenerate tetrahedron (tetra_spline.h), times rows^3
   double inv_ded, c4;  // 1/de and 4 V_T/(4 V_G) / de in FP64
   int t2, t3;          // tiles along axes 2 and 3
   int s1, s2, s3;      // cubes of the smaller tiles along each axis; the first r1, r2, r3 have one more
@@ -53,9 +54,11 @@ struct BatchItem {
   int n1, n2, n3, ne;
   float e0, de;
   int t2, t3;
-  int s1, s2, s3, r1, r2, r3;
+  int s;  // s1, s2, s3, a byte each
+  int r1, r2, r3;
   FastDiv by_ntiles, by_t2, by_t3;
   int ntiles;
+  float degenerate;
   int unit_begin;  // first global unit of this item
 };
 

@@ -11,8 +11,8 @@
 //    point's truncated powers from all tetrahedra of the tile around it and adds four entries per orbital to
 //    an LDS histogram of fourth differences (FP64 atomics, 8 lane-adds per clock and CU against 0.3 for FP32
 //    ones); four running sums down the histogram give the tile's DOS. The work per tile does not depend on
-//    the energy windows: 64^3 x 8 x 8 x 1000 took 0.33 ms with a loop over every tetrahedron's window and
-//    takes 0.18 ms; 24^3 x 8 x 8 x 4096, with windows of 75 energies, 0.04 ms. Bound by FP64 issue
+//    the energy windows: 64^3 x 8 x 8 x 1000 took 0.32 ms with a loop over every tetrahedron's window and
+//    takes 0.167 ms; 24^3 x 8 x 8 x 4096, with windows of 75 energies, 0.04 ms. Bound by FP64 issue
 //    (about 560 instructions per point, 516 of them FP64) and the LDS (120 weight reads and 32 atomics per
 //    point of 8 orbitals) in about equal parts.
 //    Tetrahedra with nearly equal corner energies go through a queue, energy by energy.
@@ -421,7 +421,7 @@ __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, General
       const int r = q / NORB, m = q - r * NORB;
       const int row = packed ? (m >> 1) : m;
       const unsigned long long* hw = &s_hist[row * RS + (r << cpl)];
-      if (MODE == 2) {
+      if constexpr (MODE == 2) {
         // exact sum of the copies in this workgroup's fixed point (|v| <= B S <= 2^62), then one
         // rounding (halves up) to the common fixed point
         long long v = 0;
@@ -546,6 +546,27 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     py = r - px * qy;
   };
 
+  // The loads of a lane's first two points are all in flight while the LDS is prepared: 0.174 -> 0.167 ms at
+  // 64^3 x 8 x 8 x 1000 (staging and the search below alone: 55 -> 44 us) against one point after the other.
+  auto grid_index = [&](int px, int py, int pz) {
+    return ((uint32_t)wrap(x0 + px, a.n1) * a.n2 + wrap(y0 + py, a.n2)) * a.n3 + wrap(z0 + pz, a.n3);
+  };
+  float ahead_e[2];
+  WT ahead_w[2][NORB];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int q = tid + i * NT;
+    if (q < np) {
+      int px, py, pz;
+      split(q, px, py, pz);
+      const uint32_t k = grid_index(px, py, pz);
+      ahead_e[i] = load_at(eps_n, k);
+#pragma unroll
+      for (int m = 0; m < NORB; ++m) ahead_w[i][m] = load_at(w_n + (int64_t)m * nk, k);
+    }
+  }
+  float first = eps_n[((int64_t)x0 * a.n2 + y0) * a.n3 + z0];
+  first = __builtin_isfinite(first) ? first : 0.0f;
   for_lanes(kKnotPad, [&](int i) { sh.u[i] = kFarKnot; });
   for_lanes(kWeightPad, [&](int i) { sh.wlo[i] = sh.whi[i] = 0.0f; });
   for_lanes(NP, [&](int i) { sh.skip[i] = 0u; });
@@ -553,15 +574,11 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     for_lanes(NP * NORB, [&](int i) { sh.w[i] = 0.0f; });
   if (tid == 0) sh.nq = 0;
   __syncthreads();
-  float first = eps_n[((int64_t)x0 * a.n2 + y0) * a.n3 + z0];
-  first = __builtin_isfinite(first) ? first : 0.0f;
   float lmin = __builtin_huge_valf(), lmax = -__builtin_huge_valf(), lbmax = 0.0f, lsum = 0.0f;
-  for_lanes(np, [&](int q) {
+  auto stage = [&](int q, float e, auto&& weight) {
     int px, py, pz;
     split(q, px, py, pz);
-    const uint32_t k = ((uint32_t)wrap(x0 + px, a.n1) * a.n2 + wrap(y0 + py, a.n2)) * a.n3 + wrap(z0 + pz, a.n3);
     const int p = px * PY + py * PZ + pz;
-    const float e = load_at(eps_n, k);
     const bool finite = __builtin_isfinite(e);
     sh.f[p] = finite ? (e - first) * a.inv_de : __builtin_huge_valf();
     if (finite) {
@@ -571,12 +588,24 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     }
 #pragma unroll
     for (int m = 0; m < NORB; ++m) {
-      const float b = weight_value(load_at(w_n + (int64_t)m * nk, k), wscale);
+      const float b = weight_value(weight(m), wscale);
       sh.w[m * NP + p] = b;
       lbmax = fmaxf(lbmax, fabsf(b));
       lsum += b;  // not a number when one of them is none
     }
-  });
+  };
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    if (tid + i * NT < np) stage(tid + i * NT, ahead_e[i], [&](int m) { return ahead_w[i][m]; });
+  for (int q0 = 2 * NT; q0 < np; q0 += NT) {  // only tiles one cube thick have so many points per lane
+    const int q = q0 + tid;
+    if (q < np) {
+      int px, py, pz;
+      split(q, px, py, pz);
+      const uint32_t k = grid_index(px, py, pz);
+      stage(q, load_at(eps_n, k), [&](int m) { return load_at(w_n + (int64_t)m * nk, k); });
+    }
+  }
   if (!(fabsf(lsum) < __builtin_huge_valf())) lbmax = __builtin_huge_valf();
   lmin = wave_min(lmin);
   lmax = wave_max(lmax);
@@ -634,7 +663,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
                             : fmin(ceil(umax), (double)a.ne) - floor(umin);
   if (!(rows_d + NE + 2 <= (double)spline_words<NORB>())) return false;
   const int base = uniform((int)floor(umin)), rows = uniform((int)rows_d);
-  const float J = (float)rows, limit = (MODE == 2 ? kDegenerateExact : kDegenerate) * J * J * J;
+  const float J = (float)rows, limit = (MODE == 2 ? kDegenerateExact : a.degenerate) * J * J * J;
 
   // Degenerate tetrahedra: their bits at their corner points, and a queue. Corners 2 and 5 belong to all six
   // of Table I, the other two run around them.
@@ -731,9 +760,10 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       double D[NE];
 #pragma unroll
       for (int i = 0; i < NE; ++i) D[i] = __builtin_fma(Q, N[i], bp * n[i]);
-      act(m - m0, row, D);
+      act(m, row, D);
     };
-#pragma unroll 1
+    // two at a time: the next one's weights are on their way (0.167 against 0.174 ms one at a time)
+#pragma unroll 2
     for (int m = m0; m < m1; ++m) orbital(m);
   };
 
@@ -825,7 +855,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     for_lanes(np, [&](int q) {
       Acc* const mine = hist + (q & (copies - 1)) * plane;
       point(q, m0, m1, scale, [&](int m, int row, const double D[NE]) {
-        Acc* h = &mine[m * RS + row];
+        Acc* h = &mine[(m - m0) * RS + row];
 #pragma unroll
         for (int i = 0; i < NE; ++i) {
           if constexpr (MODE == 2) {
@@ -962,9 +992,9 @@ __global__ __launch_bounds__(NTMAX, kWaves) void dos_batched_kernel(BatchArgs b)
   a.c4 = 4.0 * V * a.inv_ded;
   a.t2 = it.t2;
   a.t3 = it.t3;
-  a.s1 = it.s1;
-  a.s2 = it.s2;
-  a.s3 = it.s3;
+  a.s1 = it.s & 0xff;
+  a.s2 = (it.s >> 8) & 0xff;
+  a.s3 = it.s >> 16;
   a.r1 = it.r1;
   a.r2 = it.r2;
   a.r3 = it.r3;
@@ -972,6 +1002,7 @@ __global__ __launch_bounds__(NTMAX, kWaves) void dos_batched_kernel(BatchArgs b)
   a.by_t2 = it.by_t2;
   a.by_t3 = it.by_t3;
   a.ntiles = it.ntiles;
+  a.degenerate = it.degenerate;
   forward_unit<NORB, WT, 0>(a, u - it.unit_begin, sh);
 }
 

@@ -64,10 +64,10 @@ __host__ __device__ __forceinline__ float spline_gap(float a0, float a1, float b
   return m * m * fminf(e3 - e1, e4 - e2) * fminf(e4 - e1, 1.0f);
 }
 // A tetrahedron is left to the energy-by-energy sum where its spline_gap is below this times J^3: its terms
-// would lose more than about kTail of its own density at the far end of the sums. Plain sums end in
+// would lose more than the share given of its own density at the far end of the sums. Plain sums end in
 // FP32 additions and their errors average over the tetrahedra; exact ones hold 51 bits.
-constexpr float kDegenerate = 2.2e-12f;       // kTail 2e-4; 0.05 % of the tetrahedra of generic bands
-constexpr float kDegenerateExact = 1.0e-10f;  // kTail 4e-6; 0.4 %
+constexpr float kDegenerate = 2.2e-12f;       // 2e-4 of the density; 0.05 % of the tetrahedra of generic bands
+constexpr float kDegenerateExact = 1.0e-10f;  // 4e-6; 0.4 %
 
 // Nothing is scheduled across it on the device (to bound the registers of long straight-line code).
 __host__ __device__ __forceinline__ void schedule_fence() {
