@@ -41,14 +41,17 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 KERNEL_SOURCES = {
     "dos_forward_kernel": ("tetra_forward.hip", "tetra_forward_args.h", "tetra_forward_kernels.h", "tetra_spline.h",
-                           "tetra_nos_device.h", "tetra_device.h", "tetra_internal.h", "tetra_weights.h"),
+                           "tetra_spline_tile.h", "tetra_wave.h", "tetra_nos_device.h", "tetra_device.h",
+                           "tetra_internal.h", "tetra_weights.h"),
     # the adjoint pass: dos_backward_kernel and its gather pass, both in tetra_backward.hip
     "dos_backward_kernel": ("tetra_backward.hip", "tetra_device.h", "tetra_faces.h", "tetra_internal.h",
                             "tetra_weights.h"),
     "nos_kernel": ("tetra_nos.hip", "tetra_nos_kernels.h", "tetra_nos_device.h", "tetra_forward_args.h",
-                   "tetra_forward_kernels.h", "tetra_spline.h", "tetra_device.h", "tetra_internal.h",
-                   "tetra_weights.h"),
-    "chi_kernel": ("tetra_chi.hip", "tetra_chi_device.h", "tetra_device.h", "tetra_internal.h", "tetra_weights.h"),
+                   "tetra_forward_kernels.h", "tetra_spline.h", "tetra_spline_tile.h", "tetra_wave.h",
+                   "tetra_device.h", "tetra_internal.h", "tetra_weights.h"),
+    "chi_kernel": ("tetra_chi.hip", "tetra_chi_args.h", "tetra_chi_spline_kernels.h", "tetra_chi_device.h",
+                   "tetra_forward_args.h", "tetra_spline.h", "tetra_spline_tile.h", "tetra_wave.h", "tetra_device.h",
+                   "tetra_internal.h", "tetra_weights.h"),
 }
 
 

@@ -3,19 +3,18 @@
 // (Im chi_0 = -pi S), by the linear tetrahedron method of Guterding & Jeschke (arXiv:1710.10789,
 // Sec. II) with the difference energy eps_n'(k + q) - eps_n(k) in the role of the band energy.
 //
-// Work decomposition, as the DOS forward: one workgroup per (tile of TX x TY x TZ cubes, band pair
-// (n, n')), units tile-major, and each XCD takes a contiguous range of them. The tile's grid points
-// are staged in LDS with eps_n at the point, eps_n' at the point shifted by q (periodic), and the
-// product weights W_m = b_mn(k) b_mn'(k + q). Each energy pass runs two sweeps:
-//  * one lane per cube over the six tetrahedra of Table I: an occupation region that is the whole
-//    tetrahedron (band n occupied and n' empty at every corner, or the reverse; most of them) is the
-//    DOS of eps' - eps formed as in the forward kernel (sort, exact window, case split, corner weights
-//    of Sec. II.C); the other regions that may be non-empty go to a queue in LDS;
-//  * every lane over the queued regions' sub-tetrahedra: a region is clipped at eps = E_F and
-//    eps' = E_F into at most nine of them (held as barycentric rows in the parent); each takes the
-//    same DOS treatment with W formed at its vertices and its share of the volume. The regions that
-//    need clipping lie where a band crosses E_F, in a few cubes of a tile: shared out piece by piece
-//    they no longer hold one wavefront, and the workgroup behind its barrier, for the whole pass.
+// Two passes over the band pairs (n, n'), which add into the same output:
+//  * chi_spline_kernel (tetra_chi_spline_kernels.h): the tetrahedra that are occupied in one band and empty in the
+//    other at every corner, most of them, in the spline form of the DOS;
+//  * chi_kernel, here: the tetrahedra that E_F cuts in one of the bands.
+// One workgroup per (tile of TX x TY x TZ cubes, band n), or several, each with a share of the bands n', tile-major,
+// and each XCD takes a contiguous range of them. For a pair the tile's grid points are staged in LDS with eps_n at
+// the point and eps_n' at the point shifted by q (periodic); every lane goes over the six tetrahedra of Table I of
+// its cube and queues the occupation regions that have to be clipped; only then the product weights
+// W_m = b_mn(k) b_mn'(k + q) are staged. Each energy pass lists the regions' pieces (a region is clipped at eps = E_F
+// and eps' = E_F into at most nine sub-tetrahedra, held as barycentric rows in the parent), then every lane takes
+// pieces: the DOS of eps' - eps on each with W formed at its vertices and its share of the volume (sort, exact window,
+// case split, corner weights of Sec. II.C).
 // The LDS histograms hold fixed point with a power-of-two scale from a bound: the part of a
 // tetrahedron on either side of an occupation boundary has a section no larger than the whole
 // tetrahedron's, so a tetrahedron adds at most 12 V max|W| / (max - min of eps' - eps) to any bin
@@ -23,12 +22,21 @@
 // region, two orbitals per 64-bit word; otherwise one signed 64-bit histogram. The sums are exact
 // integers, so the order in which the queue is filled and worked off does not change them. One global
 // float atomic per touched (energy, orbital) bin at the end.
+//
+// 64^3 x 8 x 8 x 500: 1.72 ms when one kernel took both kinds of region (every tetrahedron's window energy by
+// energy), 1.37 ms now, 0.71 ms of it the spline pass and 0.65 ms this kernel's, bound by instruction issue: of that
+// about 0.13 ms staging and the search for regions, 0.06 ms weights, 0.17 ms listing the pieces and clearing and
+// flushing the histogram, 0.3 ms clipping and summing the pieces. Leaving the pieces in nine slots per region, two
+// or three of them filled, took 0.1 ms more, and workgroups for pairs that E_F cuts in neither band 0.15 ms.
 
+#include <algorithm>
 #include <type_traits>
 
+#include "tetra_chi_args.h"
 #include "tetra_chi_device.h"
 #include "tetra_device.h"
 #include "tetra_internal.h"
+#include "tetra_wave.h"
 #include "tetra_weights.h"
 
 namespace tetra {
@@ -37,6 +45,7 @@ namespace {
 
 constexpr int NT = kTileCubes;
 constexpr int NPMAX = kTilePointsMax;
+constexpr int QCAP = NT * 12 + 576;  // queue: the most regions a tile has, and the pieces of 64 of them
 constexpr int HCAP = 2048;  // LDS histogram capacity in 64-bit words
 constexpr int NXCD = 8;
 
@@ -49,7 +58,8 @@ struct ChiArgs {
   int q1, q2, q3;  // transfer in grid steps, reduced to [0, n)
   float ef, e0, de, inv_de, V;
   int TX, TY, TZ;
-  int t1, t2, t3, ntiles, nunits, per_xcd;
+  int t1, t2, t3, ntiles;
+  int parts, nunits, per_xcd;  // workgroups per (tile, band n), in all, per XCD
   // Energy range (smallest, largest finite value) of every (tile, band): rows [0, nb) at the tile's
   // points, rows [nb, 2 nb) at the points shifted by q; NULL where not computed.
   const float2* ranges;
@@ -58,19 +68,6 @@ struct ChiArgs {
 __device__ __forceinline__ int wrap_index(int v, int n) {
   if (v >= n) v -= n;
   if (v >= n) v %= n;
-  return v;
-}
-
-__device__ __forceinline__ float wave_min_f(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_max_f(float v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ float wave_sum_f(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
 
@@ -100,10 +97,10 @@ __global__ __launch_bounds__(NT) void chi_ranges_kernel(ChiArgs a) {
       qmax = fmaxf(qmax, eq);
     }
   }
-  kmin = wave_min_f(kmin);
-  kmax = wave_max_f(kmax);
-  qmin = wave_min_f(qmin);
-  qmax = wave_max_f(qmax);
+  kmin = wave_min(kmin);
+  kmax = wave_max(kmax);
+  qmin = wave_min(qmin);
+  qmax = wave_max(qmax);
   if ((threadIdx.x & 63) == 0) {
     const int wv = threadIdx.x >> 6;
     s_r[wv] = kmin;
@@ -126,35 +123,36 @@ __global__ __launch_bounds__(NT) void chi_ranges_kernel(ChiArgs a) {
   }
 }
 
-// Waves per SIMD the kernel is held to. With nothing of the clipping live over a sub-tetrahedron's
-// energy loop it needs 100-140 VGPRs up to 8 orbitals (139 at 8: held to 4 waves it keeps 8 values in
-// scratch, 2.00 against 2.27 ms at 3 waves for the 64^3 x 8 x 8 x 500 workload) and up to 196 at 16
-// (held to 3 waves it keeps 30 values in scratch and still beats 2 waves: 4.68 against 5.18 ms for
-// 48^3 x 16 x 16 x 500).
+// Waves per SIMD the kernel is held to: 88-128 VGPRs up to 8 orbitals, 133-168 above (20 and 40 bytes of scratch with
+// 15 and 16 orbitals, written and read with every lane active).
 constexpr int chi_waves(int norb) { return norb <= 8 ? 4 : 3; }
 
-template <int NORB, typename WT>
-__global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
-  constexpr int RS = (HCAP / NORB - 1) | 1;  // histogram row stride (one row per orbital), odd
-  __shared__ float s_e[NPMAX];
-  __shared__ float s_ep[NPMAX];
-  __shared__ float s_W[NPMAX * NORB];
-  __shared__ unsigned long long s_hist[HCAP];
-  __shared__ float s_red[8 * (NT / 64)];
-  // regions to clip, queued by the first sweep of a pass and shared out over every lane by the second:
-  // lane of the cube << 4 | tetrahedron << 1 | region (at most 6 x 2 per cube)
-  __shared__ unsigned short s_q[NT * 12];
-  __shared__ int s_qn;
+// Whether E_F cuts one of the two bands: without, every region is a whole tetrahedron or empty.
+__device__ __forceinline__ bool crosses(float emin, float emax, float pmin, float pmax, float ef) {
+  return (emin < ef && emax > ef) || (pmin < ef && pmax > ef);
+}
 
-  const int b = blockIdx.x;
-  const int unit = (b % NXCD) * a.per_xcd + b / NXCD;
-  if (unit >= a.nunits) return;
-  // Tile-major units: the band pairs of one tile follow each other, so the tile's points (every band)
-  // stay in the XCD's L2 while its pairs run.
-  const int npairs = a.nb * a.nb;
-  const int tile = unit / npairs;
-  const int pair = unit - tile * npairs;
-  const int n = pair / a.nb, np = pair - n * a.nb;
+template <int NORB>
+struct ChiShared {
+  float e[NPMAX];
+  float ep[NPMAX];
+  float W[NPMAX * NORB];
+  unsigned long long hist[HCAP];
+  float red[8 * (NT / 64)];
+  // regions to clip: lane of the cube << 4 | tetrahedron << 1 | region (at most 6 x 2 per cube); after them the
+  // pieces of some: place of the region << 4 | first piece << 2 | second piece
+  unsigned short q[QCAP];
+  int qn, pn;
+};
+
+// The pair of bands (n, np) over a tile; every lane of the workgroup calls it.
+template <int NORB, typename WT>
+__device__ __forceinline__ void chi_unit(const ChiArgs& a, int tile, int n, int np, ChiShared<NORB>& sh) {
+  constexpr int RS = (HCAP / NORB - 1) | 1;  // histogram row stride (one row per orbital), odd
+  float *const s_e = sh.e, *const s_ep = sh.ep, *const s_W = sh.W, *const s_red = sh.red;
+  unsigned long long* const s_hist = sh.hist;
+  unsigned short* const s_q = sh.q;
+  int &s_qn = sh.qn, &s_pn = sh.pn;
   const int TX = a.TX, TY = a.TY, TZ = a.TZ;
   const int PY = TY + 1, PZ = TZ + 1;
   const int NP = (TX + 1) * PY * PZ;
@@ -162,7 +160,8 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
   const int ty = (tile / a.t3) % a.t2;
   const int tx = tile / (a.t3 * a.t2);
   const int x0 = tx * TX, y0 = ty * TY, z0 = tz * TZ;
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // nothing formed from it is kept live from one pair to the next
   const int64_t nk = (int64_t)a.n1 * a.n2 * a.n3;
   const float* eps_n = a.eps + (int64_t)n * nk;
   const float* eps_p = a.eps + (int64_t)np * nk;
@@ -170,19 +169,6 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
   const WT* w_p = static_cast<const WT*>(a.w) + (int64_t)np * NORB * nk;
   const float sc_n = a.w_scale ? a.w_scale[n] : 1.0f, sc_p = a.w_scale ? a.w_scale[np] : 1.0f;
 
-  // With the first pass's ranges a unit that cannot contribute leaves before loading anything: the
-  // tables bound the staged values (their ranges include points where only one band is finite), so
-  // these tests only ever let through units that the exact ones below then drop.
-  if (a.ranges) {
-    const float2 rk = a.ranges[(int64_t)n * a.ntiles + tile];
-    const float2 rq = a.ranges[(int64_t)(a.nb + np) * a.ntiles + tile];
-    if (!(rk.x <= rk.y) || !(rq.x <= rq.y)) return;  // no finite energy in one of the bands
-    if (!region_possible(0, rk.x, rk.y, rq.x, rq.y, a.ef) && !region_possible(1, rk.x, rk.y, rq.x, rq.y, a.ef))
-      return;
-    int K0, K1;
-    range_window(rq.x - rk.y, rq.y - rk.x, a.e0, a.inv_de, a.ne, K0, K1);
-    if (K0 > K1) return;
-  }
   // Stage the tile's energies: eps_n at the point, eps_n' at the point + q; reduce the ranges of eps,
   // eps' and eps' - eps. Most (tile, band pair) units end here: no region can be occupied on one side
   // and empty on the other, or eps' - eps stays outside the energy grid; their weights are never read.
@@ -193,6 +179,7 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
     kq = ((int64_t)wrap_index(i1 + a.q1, a.n1) * a.n2 + wrap_index(i2 + a.q2, a.n2)) * a.n3 +
          wrap_index(i3 + a.q3, a.n3);
   };
+  if (tid == 0) s_qn = 0;
   float r_emin = __builtin_huge_valf(), r_emax = -__builtin_huge_valf();
   float r_pmin = __builtin_huge_valf(), r_pmax = -__builtin_huge_valf();
   float r_dmin = __builtin_huge_valf(), r_dmax = -__builtin_huge_valf();
@@ -211,8 +198,8 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
       r_dmax = fmaxf(r_dmax, ep - e);
     }
   }
-  float red[8] = {wave_min_f(r_emin), wave_max_f(r_emax), wave_min_f(r_pmin), wave_max_f(r_pmax),
-                  wave_min_f(r_dmin), wave_max_f(r_dmax), 0.0f, 0.0f};
+  float red[8] = {wave_min(r_emin), wave_max(r_emax), wave_min(r_pmin), wave_max(r_pmax),
+                  wave_min(r_dmin), wave_max(r_dmax), 0.0f, 0.0f};
   if ((tid & 63) == 0)
 #pragma unroll
     for (int i = 0; i < 6; ++i) s_red[i * (NT / 64) + (tid >> 6)] = red[i];
@@ -234,6 +221,93 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
   int J0, J1;
   range_window(red[4], red[5], a.e0, a.inv_de, a.ne, J0, J1);
   if (J0 > J1) return;
+  if (!crosses(red[0], red[1], red[2], red[3], ef)) return;
+
+  // First point of lane i's cube; false where the grid ends before it.
+  auto lane_cube = [&](int i, int& pbase) {
+    const int cz = i % TZ, cy = (i / TZ) % TY, cx = i / (TZ * TY);
+    pbase = (cx * PY + cy) * PZ + cz;
+    return (x0 + cx < a.n1) && (y0 + cy < a.n2) && (z0 + cz < a.n3);
+  };
+  auto point_offset = [PY, PZ](int s) { return (s & 1) * (PY * PZ) + ((s >> 1) & 1) * PZ + (s >> 2); };
+
+  // The regions of tetrahedron t of this lane's cube that are to be clipped, and the range of eps' - eps over it;
+  // false when there is none that can contribute to [lo, hi]. A region that is the whole tetrahedron (n occupied
+  // and n' empty at every corner for region 0, the reverse for region 1) is the spline pass's.
+  auto regions = [&](int pbase, int t, int lo, int hi, bool reg[2], float& dmin, float& dmax) {
+    const uint32_t slots = tet_slots(t);
+    float emin = __builtin_huge_valf(), emax = -emin, pmin = emin, pmax = -emin;
+    dmin = emin;
+    dmax = -emin;
+    bool fin = true;
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+      const int p = pbase + point_offset((slots >> (4 * l)) & 7);
+      const float e = s_e[p], ep = s_ep[p];
+      fin = fin && __builtin_isfinite(e) && __builtin_isfinite(ep);
+      emin = fminf(emin, e);
+      emax = fmaxf(emax, e);
+      pmin = fminf(pmin, ep);
+      pmax = fmaxf(pmax, ep);
+      dmin = fminf(dmin, ep - e);
+      dmax = fmaxf(dmax, ep - e);
+    }
+    if (!fin || !(dmax > dmin)) return false;
+    const int whole = (emax <= ef && pmin >= ef) ? 0 : (emin >= ef && pmax <= ef) ? 1 : -1;
+    reg[0] = whole != 0 && region_possible(0, emin, emax, pmin, pmax, ef);
+    reg[1] = whole != 1 && region_possible(1, emin, emax, pmin, pmax, ef);
+    if (!reg[0] && !reg[1]) return false;
+    int jlo, jhi;
+    energy_window(dmin, dmax, a.e0, a.inv_de, lo, hi, jlo, jhi);
+    return jlo <= jhi + 2;
+  };
+
+  // The regions to clip into the queue, every lane on its own cube. They lie where a band crosses E_F, in a few
+  // cubes of the tile; shared out over all lanes they do not hold one wavefront, and the workgroup behind its
+  // barrier, for the whole pass. With them a bound on any bin's |sum|: sum over their tetrahedra of 12 V max|W| /
+  // (dmax - dmin), 12 V max|W| below, and the range of eps' - eps. Narrow tetrahedra (a range below 2 de) give
+  // spikes that make B loose.
+  float bound = 0.0f, narrow = 0.0f, lo = __builtin_huge_valf(), hi = -__builtin_huge_valf();
+  if (int pbase; lane_cube(tid, pbase)) {
+#pragma unroll 1
+    for (int t = 0; t < 6; ++t) {
+      bool reg[2];
+      float dmin, dmax;
+      if (!regions(pbase, t, J0, J1, reg, dmin, dmax)) continue;
+#pragma unroll
+      for (int r = 0; r < 2; ++r)
+        if (reg[r]) s_q[atomicAdd(&s_qn, 1)] = (unsigned short)((tid << 4) | (t << 1) | r);
+      const float term = rcp(dmax - dmin);
+      bound += term;
+      if (dmax - dmin < 2.0f * a.de) narrow += term;
+      lo = fminf(lo, dmin);
+      hi = fmaxf(hi, dmax);
+    }
+  }
+  bound = wave_sum(bound);
+  narrow = wave_sum(narrow);
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  __syncthreads();  // every lane has read s_red
+  if ((tid & 63) == 0) {
+    s_red[tid >> 6] = bound;
+    s_red[(NT / 64) + (tid >> 6)] = narrow;
+    s_red[2 * (NT / 64) + (tid >> 6)] = lo;
+    s_red[3 * (NT / 64) + (tid >> 6)] = hi;
+  }
+  __syncthreads();
+  float B = 0.0f, Bn = 0.0f;
+#pragma unroll
+  for (int i = 0; i < NT / 64; ++i) {
+    B += s_red[i];
+    Bn += s_red[NT / 64 + i];
+    lo = fminf(lo, s_red[2 * (NT / 64) + i]);
+    hi = fmaxf(hi, s_red[3 * (NT / 64) + i]);
+  }
+  if (!(B > 0.0f)) return;  // nothing to clip (uniform across the block)
+  range_window(lo, hi, a.e0, a.inv_de, a.ne, J0, J1);
+  J0 = uniform(J0);
+  J1 = uniform(J1);
 
   // The weights W = b_n(k) b_n'(k + q), with the largest |W| and the smallest W.
   float r_wmax = 0.0f, r_wmin = 0.0f;
@@ -248,8 +322,8 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
       r_wmin = fminf(r_wmin, W);
     }
   }
-  r_wmax = wave_max_f(r_wmax);
-  r_wmin = wave_min_f(r_wmin);
+  r_wmax = wave_max(r_wmax);
+  r_wmin = wave_min(r_wmin);
   if ((tid & 63) == 0) {
     s_red[6 * (NT / 64) + (tid >> 6)] = r_wmax;
     s_red[7 * (NT / 64) + (tid >> 6)] = r_wmin;
@@ -264,78 +338,10 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
   }
   const float wmax = red[6], wmin = red[7];
 
-  const int cz = tid % TZ, cy = (tid / TZ) % TY, cx = tid / (TZ * TY);
-  const bool valid = (x0 + cx < a.n1) && (y0 + cy < a.n2) && (z0 + cz < a.n3);
-  const int pbase = (cx * PY + cy) * PZ + cz;
-  auto point_offset = [PY, PZ](int s) { return (s & 1) * (PY * PZ) + ((s >> 1) & 1) * PZ + (s >> 2); };
-
-  // Corner data of tetrahedron t of this lane's cube; false when it cannot contribute to [lo, hi].
-  // whole: the region that is the whole tetrahedron (n occupied and n' empty at every corner for region
-  // 0, the reverse for region 1), or -1.
-  auto corners = [&](int t, int lo, int hi, int pt[4], float e[4], float ep[4], bool reg[2], int& whole) {
-    const uint32_t slots = tet_slots(t);
-    float emin = __builtin_huge_valf(), emax = -emin, pmin = emin, pmax = -emin, dmin = emin, dmax = -emin;
-    bool fin = true;
-#pragma unroll
-    for (int l = 0; l < 4; ++l) {
-      pt[l] = pbase + point_offset((slots >> (4 * l)) & 7);
-      e[l] = s_e[pt[l]];
-      ep[l] = s_ep[pt[l]];
-      fin = fin && __builtin_isfinite(e[l]) && __builtin_isfinite(ep[l]);
-      emin = fminf(emin, e[l]);
-      emax = fmaxf(emax, e[l]);
-      pmin = fminf(pmin, ep[l]);
-      pmax = fmaxf(pmax, ep[l]);
-      dmin = fminf(dmin, ep[l] - e[l]);
-      dmax = fmaxf(dmax, ep[l] - e[l]);
-    }
-    if (!fin || !(dmax > dmin)) return false;
-    whole = (emax <= ef && pmin >= ef) ? 0 : (emin >= ef && pmax <= ef) ? 1 : -1;
-    reg[0] = region_possible(0, emin, emax, pmin, pmax, ef);
-    reg[1] = region_possible(1, emin, emax, pmin, pmax, ef);
-    if (!reg[0] && !reg[1]) return false;
-    int jlo, jhi;
-    energy_window(dmin, dmax, a.e0, a.inv_de, lo, hi, jlo, jhi);
-    return jlo <= jhi + 2;
-  };
-
-  // Bound on any bin's |sum|: sum over tetrahedra that may contribute of 12 V max|W| / (dmax - dmin).
-  // Narrow tetrahedra (a range of eps' - eps below 2 de) give spikes that make B loose.
-  float bound = 0.0f, narrow = 0.0f;
-  if (valid) {
-#pragma unroll 1
-    for (int t = 0; t < 6; ++t) {
-      int pt[4];
-      float e[4], ep[4];
-      bool reg[2];
-      int whole;
-      if (!corners(t, J0, J1, pt, e, ep, reg, whole)) continue;
-      float dmin = ep[0] - e[0], dmax = dmin;
-#pragma unroll
-      for (int l = 1; l < 4; ++l) {
-        dmin = fminf(dmin, ep[l] - e[l]);
-        dmax = fmaxf(dmax, ep[l] - e[l]);
-      }
-      const float term = 12.0f * a.V * wmax * rcp(dmax - dmin);
-      bound += term;
-      if (dmax - dmin < 2.0f * a.de) narrow += term;
-    }
-  }
-  bound = wave_sum_f(fminf(bound, 1.0e37f));
-  narrow = wave_sum_f(fminf(narrow, 1.0e37f));
-  __syncthreads();  // every lane has read s_red
-  if ((tid & 63) == 0) {
-    s_red[tid >> 6] = bound;
-    s_red[(NT / 64) + (tid >> 6)] = narrow;
-  }
-  __syncthreads();
-  float B = 0.0f, Bn = 0.0f;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) {
-    B += s_red[i];
-    Bn += s_red[NT / 64 + i];
-  }
-  if (!(B > 0.0f)) return;  // nothing to add (uniform across the block)
+  const float c12 = 12.0f * a.V * wmax;
+  B = fminf(B * c12, 3.0e38f);
+  Bn = fminf(Bn * c12, 3.0e38f);
+  if (!(B > 0.0f)) return;
   // Packed: within one region every contribution is non-negative when the weights are (corner weights
   // and barycentric coordinates are), so each region gets a histogram of its own with two orbitals per
   // 64-bit word as 32-bit fields (B S <= 2^30, no carry between fields) and the result is their
@@ -343,9 +349,8 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
   const bool packed = wmin >= 0.0f && Bn <= 0.5f * B;  // uniform across the block
   int bexp;
   frexpf(fminf(B, 3.0e38f), &bexp);  // B <= 2^bexp
-  const int sexp = min((packed ? 30 : 62) - bexp, 126);
-  const float VS = a.V * ldexpf(1.0f, sexp);  // V_T/(4 V_G) in units of the fixed point
-  const double inv_S = ldexp(1.0, -sexp);
+  const int sexp = uniform(min((packed ? 30 : 62) - bexp, 126));
+  const float VS = uniform(a.V * ldexpf(1.0f, sexp));  // V_T/(4 V_G) in units of the fixed point
 
   auto passes = [&](auto packed_tag) {
     constexpr bool PACKED = decltype(packed_tag)::value;
@@ -399,127 +404,84 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
     for (int c0 = J0; c0 <= J1; c0 += RSX) {
       const int c1 = min(c0 + RSX - 1, J1);
       const int L = c1 - c0 + 1;
+      int tid = threadIdx.x;  // opaque again: the addresses formed from it are formed in each pass
+      asm volatile("" : "+v"(tid));
       const int rows = PACKED ? NPAIR : NORB;
       for (int q = tid; q < rows * L; q += NT) {
         const int m = q / L;
         s_hist[m * RSX + (q - m * L)] = 0ull;
         if (PACKED) hist_m[m * RSX + (q - m * L)] = 0ull;
       }
-      if (tid == 0) s_qn = 0;
       __syncthreads();
-      // First sweep, every lane on its own cube: the regions that are the whole tetrahedron, most of
-      // them, as the forward kernel forms a DOS (the corners sorted with their points, the weights read
-      // in sorted order, no clipping), and the other regions queued. The regions that need clipping lie where a band crosses E_F, in a
-      // few cubes of the tile; sharing them out over all lanes keeps them from holding one wavefront,
-      // and the workgroup behind its barrier, for the whole pass.
-      if (valid) {
-#pragma unroll 1
-        for (int t = 0; t < 6; ++t) {
-          int pt[4];
-          float e[4], ep[4];
-          bool reg[2];
-          int whole;
-          if (!corners(t, c0, c1, pt, e, ep, reg, whole)) continue;
-#pragma unroll
-          for (int r = 0; r < 2; ++r)
-            if (reg[r] && r != whole) s_q[atomicAdd(&s_qn, 1)] = (unsigned short)((tid << 4) | (t << 1) | r);
-          if (whole < 0) continue;
-          float d[4];
-#pragma unroll
-          for (int c = 0; c < 4; ++c) d[c] = ep[c] - e[c];
-          sort4(d, pt);
-          int jlo, jhi;
-          energy_window(d[0], d[3], a.e0, a.inv_de, c0, c1, jlo, jhi);
-          if (jlo > jhi + 2) continue;
-          const TetSetup cs = tet_setup(d, a.e0, VS);
-          tet_window(cs, a.de, c0, c1, jlo, jhi);
-          if (jlo > jhi) continue;
-          float ws[4][NORB];
-#pragma unroll
-          for (int l = 0; l < 4; ++l)
-#pragma unroll
-            for (int m = 0; m < NORB; ++m) ws[l][m] = s_W[pt[l] * NORB + m];
-          int jA, jB;
-          case_split(cs, a.de, a.inv_de, jlo, jhi, jA, jB);
-          float coef[4][4];
-          if (jB > jA) corner_dos_B_coeffs(cs, VS, coef);
-          const float sign = whole == 0 ? 1.0f : -1.0f;
-          unsigned long long* hreg = (PACKED && whole == 1) ? hist_m : s_hist;
-          for (int j = jlo; j <= jhi; ++j) {
-            float g[4];
-            corner_g(cs, coef, j, jA, jB, g);
-            deposit(&hreg[j - c0], g, ws, sign);
-          }
-        }
-      }
-      __syncthreads();
-      // Second sweep: the queued regions, clipped at the two occupation boundaries into at most 3 x 3
-      // sub-tetrahedra. The lanes take (first piece, second piece, region) slots, piece-major: a
-      // region's first slot holds a piece unless the region is empty, the others only for some
-      // regions, so the slots with work stay together and a wavefront whose slots hold no piece
-      // leaves early. Each slot redoes its region's
-      // planes and first clipping from LDS (nothing of the clipping stays live over a piece's energy
-      // loop) and leaves early if its piece does not exist.
-      const int nq = s_qn;
+      // The queued regions, clipped at the two occupation boundaries into at most 3 x 3 sub-tetrahedra, as many
+      // regions at a time as the rest of the queue holds pieces for. First the pieces are listed, a lane per
+      // (first piece, region), so that every lane then has a piece: of nine slots per region two or three hold
+      // one, spread over all of a wavefront's slots. Each piece redoes its region's planes and first
+      // clipping from LDS (nothing of the clipping stays live over a piece's energy loop).
+      const int nq = s_qn, most = (QCAP - nq) / 9;
       constexpr float I[4][4] = {{1.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 1.0f, 0.0f, 0.0f},
                                  {0.0f, 0.0f, 1.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 1.0f}};
-#pragma unroll 1
-      for (int ip = tid; ip < 9 * nq; ip += NT) {
-        const int piece = ip / nq, iq = ip - piece * nq;
-        const int ia = piece / 3, ib = piece - 3 * ia;
-        const int item = s_q[iq];
+      // A region's corners: their difference energies dd, points q and occupation planes (f1, f2c <= 0 inside).
+      auto region = [&](int item, float dd[4], int q[4], float f1[4], float f2c[4]) {
         const int it = item >> 4, t = (item >> 1) & 7, r = item & 1;
         const int qz = it % TZ, qy = (it / TZ) % TY, qx = it / (TZ * TY);
         const int qbase = (qx * PY + qy) * PZ + qz;
-        // Occupation planes at the corners (f1, f2c <= 0 inside), the difference energies dd and the
-        // corners' points, reordered so that the corners inside the first plane come first: the first
-        // clipping then starts from the identity, whose unit rows fold into constants.
-        float f1[4], f2c[4], dd[4];
-        int q[4];
-        {
-          const uint32_t slots = tet_slots(t);
-          float er[4], epr[4];
+        const uint32_t slots = tet_slots(t);
+        float er[4], epr[4];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            q[c] = qbase + point_offset((slots >> (4 * c)) & 7);
-            er[c] = s_e[q[c]];
-            epr[c] = s_ep[q[c]];
-          }
-          region_planes(r, er, epr, ef, f1, f2c);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) dd[c] = epr[c] - er[c];
+        for (int c = 0; c < 4; ++c) {
+          q[c] = qbase + point_offset((slots >> (4 * c)) & 7);
+          er[c] = s_e[q[c]];
+          epr[c] = s_ep[q[c]];
         }
-        const int ni1 = (f1[0] <= 0.0f) + (f1[1] <= 0.0f) + (f1[2] <= 0.0f) + (f1[3] <= 0.0f);
-        if (ia >= clip_pieces(ni1)) continue;
+        region_planes(r, er, epr, ef, f1, f2c);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) dd[c] = epr[c] - er[c];
+        return (f1[0] <= 0.0f) + (f1[1] <= 0.0f) + (f1[2] <= 0.0f) + (f1[3] <= 0.0f);
+      };
+      // Vertices A of its piece ia and the second plane f2 at them. The corners are reordered so that those inside
+      // the first plane come first: the clipping then starts from the identity, whose unit rows fold into constants.
+      auto first_piece = [&](int ni1, int ia, float dd[4], int q[4], float f1[4], float f2c[4], float A[4][4],
+                             float f2[4]) {
         if (ni1 > 0 && ni1 < 4) inside_first_corners(f1, f2c, dd, q);
-        float A[4][4], f2[4];
-        if (ni1 == 4) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) A[i][c] = I[i][c];
-        } else {
-          clip_piece(I, f1, ni1, ia, A);
-        }
+        clip_piece(I, f1, ni1, ia, A);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           f2[i] = __builtin_fmaf(A[i][0], f2c[0], __builtin_fmaf(A[i][1], f2c[1],
                                  __builtin_fmaf(A[i][2], f2c[2], A[i][3] * f2c[3])));
-        const int ni2 = (f2[0] <= 0.0f) + (f2[1] <= 0.0f) + (f2[2] <= 0.0f) + (f2[3] <= 0.0f);
+        return (f2[0] <= 0.0f) + (f2[1] <= 0.0f) + (f2[2] <= 0.0f) + (f2[3] <= 0.0f);
+      };
+#pragma unroll 1
+      for (int i0 = 0; i0 < nq; i0 += most) {
+      const int nr = min(most, nq - i0);
+      if (tid == 0) s_pn = 0;
+      __syncthreads();
+#pragma unroll 1
+      for (int ip = tid; ip < 3 * nr; ip += NT) {
+        const int ia = (ip >= nr) + (ip >= 2 * nr), iq = i0 + ip - ia * nr;
+        float dd[4], A[4][4], f1[4], f2[4], f2c[4];
+        int q[4];
+        const int ni1 = region(s_q[iq], dd, q, f1, f2c);
+        if (ia >= clip_pieces(ni1)) continue;
+        const int count = clip_pieces(first_piece(ni1, ia, dd, q, f1, f2c, A, f2));
+        unsigned short* to = &s_q[nq + atomicAdd(&s_pn, count)];
+        for (int ib = 0; ib < count; ++ib) to[ib] = (unsigned short)(iq << 4 | ia << 2 | ib);
+      }
+      __syncthreads();
+      const int pieces = s_pn;
+#pragma unroll 1
+      for (int ip = tid; ip < pieces; ip += NT) {
+        const int entry = s_q[nq + ip], ia = (entry >> 2) & 3, ib = entry & 3, item = s_q[entry >> 4], r = item & 1;
+        float dd[4], A[4][4], f1[4], f2[4], f2c[4];
+        int q[4];
+        const int ni1 = region(item, dd, q, f1, f2c);
+        if (ia >= clip_pieces(ni1)) continue;
+        const int ni2 = first_piece(ni1, ia, dd, q, f1, f2c, A, f2);
         if (ib >= clip_pieces(ni2)) continue;
         if (ni2 > 0 && ni2 < 4) inside_first(A, f2);
         float S[4][4];
-        float frac;
-        if (ni2 == 4) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) S[i][c] = A[i][c];
-          frac = ni1 == 4 ? 1.0f : sub_volume(S);
-        } else {
-          clip_piece(A, f2, ni2, ib, S);
-          frac = sub_volume(S);
-        }
+        clip_piece(A, f2, ni2, ib, S);
+        const float frac = sub_volume(S);
         if (!(frac > 0.0f)) continue;
         float d[4];
 #pragma unroll
@@ -561,6 +523,7 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
         }
       }
       __syncthreads();
+      }
       for (int q = tid; q < L * NORB; q += NT) {
         const int rr = q / NORB, m = q - rr * NORB;
         double v;
@@ -572,7 +535,7 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
         } else {
           v = (double)(long long)s_hist[m * RSX + rr];
         }
-        if (v != 0.0) unsafeAtomicAdd(&a.out[(int64_t)(c0 + rr) * NORB + m], (float)(v * inv_S));
+        if (v != 0.0) unsafeAtomicAdd(&a.out[(int64_t)(c0 + rr) * NORB + m], (float)ldexp(v, -sexp));
       }
       __syncthreads();
     }
@@ -583,8 +546,48 @@ __global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
     passes(std::false_type{});
 }
 
+// A workgroup takes every parts-th of the bands n' that can contribute with its band n over its tile. With the
+// first pass's ranges the others cost nothing: the table's ranges bound the staged values (they include points
+// where only one band is finite), so its tests only ever let through pairs that the unit's own then drop.
+template <int NORB, typename WT>
+__global__ __launch_bounds__(NT, chi_waves(NORB)) void chi_kernel(ChiArgs a) {
+  __shared__ ChiShared<NORB> sh;
+  const int b = blockIdx.x;
+  const int unit = (b % NXCD) * a.per_xcd + b / NXCD;  // tile-major: the tile's points stay in the XCD's L2
+  if (unit >= a.nunits) return;
+  const int per_tile = a.nb * a.parts, tile = unit / per_tile, r = unit - tile * per_tile;
+  const int n = r / a.parts, part = r - n * a.parts;
+  int k = 0;
+  for (int n0 = 0; n0 < a.nb; n0 += 64) {
+    int lane = threadIdx.x;
+    asm volatile("" : "+v"(lane));
+    const int np = n0 + (lane & 63);
+    bool can = np < a.nb;
+    if (can && a.ranges) {
+      const float2 rk = a.ranges[(int64_t)n * a.ntiles + tile];
+      const float2 rq = a.ranges[(int64_t)(a.nb + np) * a.ntiles + tile];
+      int K0, K1;
+      range_window(rq.x - rk.y, rq.y - rk.x, a.e0, a.inv_de, a.ne, K0, K1);
+      can = rk.x <= rk.y && rq.x <= rq.y && K0 <= K1 && crosses(rk.x, rk.y, rq.x, rq.y, a.ef) &&
+            (region_possible(0, rk.x, rk.y, rq.x, rq.y, a.ef) || region_possible(1, rk.x, rk.y, rq.x, rq.y, a.ef));
+    }
+    for (uint64_t live = __ballot(can); live; live &= live - 1) {
+      if (k++ % a.parts != part) continue;
+      chi_unit<NORB, WT>(a, tile, n, n0 + __builtin_ctzll(live), sh);
+      __syncthreads();
+    }
+  }
+}
+
 template <int NORB>
-hipError_t launch_chi(const ChiArgs& a, int wtype, int grid, hipStream_t s) {
+hipError_t launch_chi(const ChiArgs& a, ChiSplineArgs& c, int wtype, int grid, hipStream_t s) {
+  const int64_t units = (int64_t)c.f.ntiles * c.nb * c.parts;
+  for (c.first = 0; c.first < units; c.first += c.nunits) {
+    c.nunits = (int)std::min<int64_t>(units - c.first, 1 << 30);
+    c.per_xcd = (c.nunits + NXCD - 1) / NXCD;
+    const hipError_t e = launch_chi_spline<NORB>(c, s);
+    if (e != hipSuccess) return e;
+  }
   if (wtype == TETRA_W_F16)
     hipLaunchKernelGGL((chi_kernel<NORB, _Float16>), dim3(grid), dim3(NT), 0, s, a);
   else if (wtype == TETRA_W_C32)
@@ -635,10 +638,33 @@ hipError_t chi(const tetra_desc& d, int q1, int q2, int q3, float e_fermi, const
   a.t2 = (d.n2 + sh.y - 1) / sh.y;
   a.t3 = (d.n3 + sh.z - 1) / sh.z;
   a.ntiles = a.t1 * a.t2 * a.t3;
-  a.nunits = (int)chi_units(d, shape);
+  // Workgroups per (tile, band n): more of them even out the pairs that do contribute, a few per (tile, n); each
+  // takes its time to start, whether it finds a pair or not (10 ns for one of the spline pass). 64^3 x 8 x 8 x 500:
+  // spline pass 0.82, 0.75, 0.71, 0.84, 0.98 ms for 1, 2, 3, 4, 8, clipping 0.89, 0.71, 0.83 ms for 1, 2, 4. Up to
+  // one per pair on small grids.
+  auto parts = [&](int64_t ntiles, int aim) {
+    return (int)std::min<int64_t>(d.nb, std::max<int64_t>(1, aim / (ntiles * d.nb)));
+  };
+  a.parts = parts(a.ntiles, 16384);
+  a.nunits = a.ntiles * d.nb * a.parts;
   a.per_xcd = (a.nunits + NXCD - 1) / NXCD;
   const int grid = a.per_xcd * NXCD;
   a.ranges = static_cast<const float2*>(ranges_ws);
+  ChiSplineArgs c;
+  c.f = forward_args(d, eps, w, wtype, w_scale, out, 0);
+  c.nb = d.nb;
+  c.parts = parts(c.f.ntiles, 12288);
+  c.q1 = a.q1;
+  c.q2 = a.q2;
+  c.q3 = a.q3;
+  c.ef = e_fermi;
+  c.ranges = a.ranges;
+  c.TX = a.TX;
+  c.TY = a.TY;
+  c.TZ = a.TZ;
+  c.u2 = a.t2;
+  c.u3 = a.t3;
+  c.ut = a.ntiles;
   hipError_t e = fill_zero(out, (int64_t)d.ne * d.norb, s);
   if (e != hipSuccess) return e;
   if (ranges_ws) {
@@ -648,7 +674,7 @@ hipError_t chi(const tetra_desc& d, int q1, int q2, int q3, float e_fermi, const
   switch (d.norb) {
 #define TETRA_CASE(N) \
   case N:             \
-    return launch_chi<N>(a, wtype, grid, s);
+    return launch_chi<N>(a, c, wtype, grid, s);
     TETRA_CASE(1) TETRA_CASE(2) TETRA_CASE(3) TETRA_CASE(4) TETRA_CASE(5) TETRA_CASE(6) TETRA_CASE(7)
     TETRA_CASE(8) TETRA_CASE(9) TETRA_CASE(10) TETRA_CASE(11) TETRA_CASE(12) TETRA_CASE(13)
     TETRA_CASE(14) TETRA_CASE(15) TETRA_CASE(16)

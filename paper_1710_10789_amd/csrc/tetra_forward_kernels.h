@@ -41,124 +41,21 @@
 #include "tetra_device.h"
 #include "tetra_forward_args.h"
 #include "tetra_nos_device.h"
-#include "tetra_spline.h"
+#include "tetra_spline_tile.h"
 #include "tetra_weights.h"
 
 namespace tetra {
 
 namespace {
 
-constexpr int kSide = 8;                  // largest tile side, in cubes
-constexpr int NTMAX = kSide * kSide * kSide;  // lanes of the largest workgroup: one per cube
-constexpr int NWMAX = NTMAX / 64;
-constexpr int PZ = kSide + 1, PY = PZ * PZ;   // strides of the tile's grid points along axes 2 and 1
-constexpr int NP = PZ * PZ * PZ;
 // Words of the general form's LDS histogram.
 template <int NORB>
 constexpr int fwd_hist_words() { return NORB <= 8 ? 1280 : NORB == 16 ? 1344 : 2048; }
-// Two workgroups of eight waves per CU: four waves per SIMD, 80 KB of LDS each.
-constexpr int kWaves = 4;
-constexpr int kLdsBytes = 81920;
-constexpr int NXCD = 8;
-
-// Global float add without a compare-and-swap loop (device memory from hipMalloc).
-__device__ __forceinline__ void atomic_add_global(float* p, float v) { unsafeAtomicAdd(p, v); }
-
-__device__ __forceinline__ int wrap(int v, int n) {
-  if (v >= n) v -= n;
-  if (v >= n) v %= n;
-  return v;
-}
-
-// A value that is the same in every lane, as a scalar.
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float uniform(float v) { return __int_as_float(uniform(__float_as_int(v))); }
-__device__ __forceinline__ double uniform(double v) {
-  return __hiloint2double(uniform(__double2hiint(v)), uniform(__double2loint(v)));
-}
-
-// Reduction over the wave by row shifts within 16 lanes and two broadcasts; every lane gets the result.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_f32(float v) {
-  const int x = __float_as_int(v);
-  return __int_as_float(__builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xf, false));  // lanes without a source: their own
-}
-template <typename F>
-__device__ __forceinline__ float wave_reduce(float v, F&& f) {
-  v = f(v, dpp_f32<0x111, 0xf>(v));  // row_shr:1, 2, 4, 8
-  v = f(v, dpp_f32<0x112, 0xf>(v));
-  v = f(v, dpp_f32<0x114, 0xf>(v));
-  v = f(v, dpp_f32<0x118, 0xf>(v));
-  v = f(v, dpp_f32<0x142, 0xa>(v));  // row_bcast:15 into rows 1 and 3
-  v = f(v, dpp_f32<0x143, 0xc>(v));  // row_bcast:31 into rows 2 and 3
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-__device__ __forceinline__ float wave_min(float v) {
-  return wave_reduce(v, [](float a, float b) { return fminf(a, b); });
-}
-__device__ __forceinline__ float wave_max(float v) {
-  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
-}
-__device__ __forceinline__ float wave_sum(float v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-
 // Common fixed point of the exact mode: with E the largest bound exponent of any workgroup (each
 // workgroup's bins sum to at most 2^E in magnitude) and L = ceil(log2(workgroups)), the total of any
 // bin is below 2^(E + L), so the scale 2^(62 - E - L) keeps every partial and total sum of the
 // 64-bit two's-complement accumulator in range.
 __device__ __forceinline__ int exact_scale_exp(int gexp, int lg_units) { return 62 - gexp - lg_units; }
-
-// One work unit (tile, band) of the forward pass; every lane of the workgroup calls it.
-// MODE 0: DOS with per-workgroup scales, flushed with float atomics;
-// 1: only the workgroup's bound exponent, into *gexp (atomicMax: independent of the order);
-// 2: DOS with per-workgroup scales as in mode 0; each bin's exact per-workgroup sum is rounded once
-//    to the common fixed point fixed by *gexp and added to gacc with a 64-bit integer atomic. Both
-//    steps are independent of the order in which workgroups run, so the result is bitwise
-//    reproducible.
-// Tile of a work unit: first cube and number of cubes along each axis (the grid's sides are dealt to the
-// tiles as evenly as they go).
-struct Tile {
-  int x0, y0, z0, cx, cy, cz;
-};
-__device__ __forceinline__ int divide(uint32_t n, FastDiv d) { return (int)(((uint64_t)n * d.m) >> d.s); }
-__device__ __forceinline__ Tile unit_tile(const FwdArgs& a, int unit, int& band) {
-  band = divide(unit, a.by_ntiles);
-  const int tile = unit - band * a.ntiles;
-  const int r = divide(tile, a.by_t3), tz = tile - r * a.t3;
-  const int tx = divide(r, a.by_t2), ty = r - tx * a.t2;
-  Tile t;
-  t.x0 = tx * a.s1 + min(tx, a.r1);
-  t.cx = a.s1 + (tx < a.r1);
-  t.y0 = ty * a.s2 + min(ty, a.r2);
-  t.cy = a.s2 + (ty < a.r2);
-  t.z0 = tz * a.s3 + min(tz, a.r3);
-  t.cz = a.s3 + (tz < a.r3);
-  return t;
-}
-
-// q / d for q < 1024 and d <= 9 by a multiplication (inv = small_inverse(d)).
-__device__ __forceinline__ int small_inverse(int d) { return 65536 / d + 1; }
-__device__ __forceinline__ int small_div(int q, int inv) { return (q * inv) >> 16; }
-
-// p[k] with a 32-bit byte offset from a uniform pointer.
-template <typename T>
-__device__ __forceinline__ T load_at(const T* p, uint32_t k) {
-  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (uint32_t)(k * (uint32_t)sizeof(T)));
-}
-
-// f(i) for i < n over the workgroup's lanes. The trip count is uniform, and the lane index opaque in every
-// call, so that nothing derived from it stays live (or spilled) between the loops of a unit.
-template <typename F>
-__device__ __forceinline__ void for_lanes(int n, F&& f, bool reverse = false) {
-  const int nt = blockDim.x;
-  int tid = threadIdx.x;
-  if (reverse) tid = nt - 1 - tid;
-  asm volatile("" : "+v"(tid));
-  for (int i0 = 0; i0 < n; i0 += nt)
-    if (i0 + tid < n) f(i0 + tid);
-}
 
 // Shared memory and body of the general form.
 template <int NORB>
@@ -169,6 +66,13 @@ struct GeneralShared {
   float red[4 * NWMAX];
 };
 
+// One work unit (tile, band) of the forward pass in the general form; every lane of the workgroup calls it.
+// MODE 0: DOS with per-workgroup scales, flushed with float atomics;
+// 1: only the workgroup's bound exponent, into *gexp (atomicMax: independent of the order);
+// 2: DOS with per-workgroup scales as in mode 0; each bin's exact per-workgroup sum is rounded once
+//    to the common fixed point fixed by *gexp and added to gacc with a 64-bit integer atomic. Both
+//    steps are independent of the order in which workgroups run, so the result is bitwise
+//    reproducible.
 template <int NORB, typename WT, int MODE>
 __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, GeneralShared<NORB>& sh) {
   constexpr int NPAIR = (NORB + 1) / 2;
@@ -448,48 +352,9 @@ __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, General
   }
 }
 
-
 // ---------------------------------------------------------------------------------------------
 // Spline form (tetra_spline.h): one lane per grid point of the tile instead of one per cube.
 
-// A lane's share of a 64-lane inclusive running sum, by row shifts within 16 lanes and two broadcasts.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xf, true);
-  return (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_of(double v) {
-  return __longlong_as_double((long long)dpp64<CTRL, ROWS>((uint64_t)__double_as_longlong(v)));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ long long dpp_of(long long v) {
-  return (long long)dpp64<CTRL, ROWS>((uint64_t)v);
-}
-template <typename T>
-__device__ __forceinline__ T wave_scan(T v) {
-  v += dpp_of<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
-  v += dpp_of<0x112, 0xf>(v);
-  v += dpp_of<0x114, 0xf>(v);
-  v += dpp_of<0x118, 0xf>(v);
-  v += dpp_of<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-  v += dpp_of<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
-  return v;
-}
-__device__ __forceinline__ double last_lane(double v) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
-                          __builtin_amdgcn_readlane(__double2loint(v), 63));
-}
-__device__ __forceinline__ long long last_lane(long long v) {
-  return __double_as_longlong(last_lane(__longlong_as_double(v)));
-}
-
-constexpr int SZ = PZ + 1, SY = PZ * SZ + SZ;     // strides of the knots, a far one at the end of every line and plane
-constexpr int kKnotMargin = SY + SZ + 1;        // the furthest neighbour offset
-constexpr int kKnotPad = PZ * SY + 2 * kKnotMargin;
-constexpr int kWeightPad = PY + PZ + 1;         // words before and after the weights that neighbour offsets reach
-constexpr int kQueue = 256;                     // degenerate tetrahedra of a unit summed energy by energy
 template <int NORB>
 struct SplineFixed {
   double u[kKnotPad];  // knots: energies in grid steps
@@ -720,17 +585,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     if (!(ju - base < (double)rows)) return;  // above the last row (or not finite)
     double M[kNeighbours];
     const int p = px * PY + py * PZ + pz;
-#pragma unroll
-    for (int u = 0; u < kNeighbours; ++u) {
-      int dx, dy, dz;
-      neighbour_offset(u, dx, dy, dz);
-      M[u] = up[dx * SY + dy * SZ + dz] - u0;
-    }
-#pragma unroll
-    for (int u = 0; u < kNeighbours; ++u) {
-      M[u] = rcp64(M[u]);
-      if (u % 7 == 6) schedule_fence();  // a few at a time: fewer registers
-    }
+    knot_reciprocals(up, u0, M);
     const uint32_t skip = sh.skip[p];
     const double T = __any(skip != 0u) ? knot_coefs_skip(M, skip) : knot_coefs(M);
     double Ms = 0.0;
@@ -748,15 +603,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     auto orbital = [&](int m) {
       const float* w = sh.w + m * NP + p;
       const double bp = w[0];
-      double Q = -Ms * bp, Q1 = 0.0;
-#pragma unroll
-      for (int u = 0; u < kNeighbours; ++u) {
-        int dx, dy, dz;
-        neighbour_offset(u, dx, dy, dz);
-        double& q = (u & 1) ? Q1 : Q;
-        q = __builtin_fma(M[u], (double)w[dx * PY + dy * PZ + dz], q);
-      }
-      Q += Q1;
+      const double Q = knot_contract(M, Ms, w);
       double D[NE];
 #pragma unroll
       for (int i = 0; i < NE; ++i) D[i] = __builtin_fma(Q, N[i], bp * n[i]);
@@ -811,21 +658,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
         put(j, w1[0] - w0[0], w1[1] - w0[1], w1[2] - w0[2], w1[3] - w0[3]);
       }
     } else {
-      int jlo, jhi;
-      energy_window(e[0], e[3], a.e0, a.inv_de, 0, a.ne - 1, jlo, jhi);
-      const TetSetup cs = tet_setup(e, a.e0, a.V);
-      tet_window(cs, a.de, 0, a.ne - 1, jlo, jhi);
-      int jA, jB;
-      case_split(cs, a.de, a.inv_de, jlo, jhi, jA, jB);
-      float coef[4][4];
-      if (jB > jA) corner_dos_B_coeffs(cs, a.V, coef);
-      for (int j = jlo + (i16 & 15); j <= jhi; j += 16) {
-        float g[4];
-        if (j <= jA) corner_dos_A(cs, local_x(cs, j, a.de), g);
-        else if (j <= jB) corner_dos_B_poly(coef, local_z(cs, j, a.de), g);
-        else corner_dos_C(cs, local_y(cs, j, a.de), g);
-        put(j, g[0], g[1], g[2], g[3]);
-      }
+      tet_energies(e, a, 0, a.ne - 1, i16 & 15, 16, [&](int j, const float g[4]) { put(j, g[0], g[1], g[2], g[3]); });
     }
   };
 
@@ -877,33 +710,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       });
     }, true);
     __syncthreads();
-    // Four running sums down each orbital's column, 64 rows at a time.
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    for (int m = wave; m < gm; m += NW) {
-      Acc c[4] = {Acc(0), Acc(0), Acc(0), Acc(0)};
-      for (int r0 = 0; r0 < rows; r0 += 128) {
-        const int r = r0 + 2 * lane;
-        Acc* hm = hist + m * RS + r;
-        Acc v0 = Acc(0), v1 = Acc(0);
-        if (r < rows)  // a row more than there are is read and written at most (RS >= rows + 5)
-          for (int k = 0; k < copies; ++k) {
-            v0 += hm[k * plane];
-            v1 += hm[k * plane + 1];
-          }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          v1 += v0;
-          const Acc t = wave_scan(v1) + c[k];
-          c[k] = last_lane(t);
-          v0 += t - v1;
-          v1 = t;
-        }
-        if (r < rows) {
-          hm[0] = v0;
-          hm[1] = v1;
-        }
-      }
-    }
+    running_sums(hist, gm, RS, plane, copies, rows);
     __syncthreads();
     const int lo = max(-base, 0);
     if (INC && lo > 0 && a.shift == 0) {  // increments below the grid count at its first energy
@@ -964,7 +771,6 @@ __global__ __launch_bounds__(NTMAX, kWaves) void dos_forward_kernel(FwdArgs a) {
 // Batched forward: one launch over the flattened (item, band, tile) units of up to kMaxBatch problems with
 // the same orbital count, a workgroup per unit.
 
-
 template <int NORB, typename WT>
 __global__ __launch_bounds__(NTMAX, kWaves) void dos_batched_kernel(BatchArgs b) {
   __shared__ FwdShared<NORB> sh;
@@ -1024,8 +830,6 @@ hipError_t launch_fwd_mode(const FwdArgs& a, int grid, hipStream_t s) {
     hipLaunchKernelGGL((dos_forward_kernel<NORB, float, MODE>), dim3(grid), dim3(a.lanes), 0, s, a);
   return hipGetLastError();
 }
-
-
 
 // dos = acc / S with S the common scale of mode 2 (all zero when no workgroup had anything to add).
 __global__ void fixed_to_float_kernel(const unsigned long long* acc, const int* gexp, int lg_units, float* dos,
