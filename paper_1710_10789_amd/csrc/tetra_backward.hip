@@ -35,7 +35,7 @@ namespace tetra {
 
 namespace {
 
-constexpr int NT = kTileCubes;      // one lane per cube of the tile
+constexpr int NT = kTileCubes;      // one lane per cube of the largest tiles
 constexpr int NPMAX = kTilePointsMax;  // grid points (cube corners) of the largest tile shape
 constexpr int HCAP = 4096;        // LDS capacity for the rows of G, in floats
 constexpr int NXCD = 8;
@@ -52,7 +52,7 @@ struct BwdArgs {
   int wtype;
   int n1, n2, n3, ne;
   float e0, de, inv_de, V;
-  int TX, TY, TZ;  // cubes per tile along grid axes 1, 2, 3 (TX*TY*TZ = NT)
+  int TX, TY, TZ;  // cubes per tile along grid axes 1, 2, 3
   int t1, t2, t3;
   int ntiles, nunits, per_xcd;
 };
@@ -132,8 +132,8 @@ __global__ __launch_bounds__(NT) void dos_backward_kernel(BwdArgs a) {
   if (emin <= emax) range_window(emin, emax, a.e0, a.inv_de, a.ne, J0, J1);
 
   const int cz = tid % TZ, cy = (tid / TZ) % TY, cx = tid / (TZ * TY);
-  const bool active = (x0 + cx < a.n1) && (y0 + cy < a.n2) && (z0 + cz < a.n3);
-  const int pbase = (cx * PY + cy) * PZ + cz;
+  const bool active = cx < TX && (x0 + cx < a.n1) && (y0 + cy < a.n2) && (z0 + cz < a.n3);
+  const int pbase = cx < TX ? (cx * PY + cy) * PZ + cz : 0;  // lanes past the tile's cubes have no work of their own
   auto point_offset = [PY, PZ](int s) { return (s & 1) * (PY * PZ) + ((s >> 1) & 1) * PZ + (s >> 2); };
 
   // Corners 2 and 5 of the cube (its body diagonal) belong to all six tetrahedra of Table I: their sums
@@ -468,12 +468,16 @@ hipError_t backward(const tetra_desc& d, const float* eps, const void* w, int wt
   a.inv_de = 1.0f / d.de;
   a.V = (float)(1.0 / (24.0 * (double)d.n1 * d.n2 * d.n3));
   const TileShape sh = tile_shape(shape);
-  a.TX = sh.x;
-  a.TY = sh.y;
-  a.TZ = sh.z;
   a.t1 = (d.n1 + sh.x - 1) / sh.x;
   a.t2 = (d.n2 + sh.y - 1) / sh.y;
   a.t3 = (d.n3 + sh.z - 1) / sh.z;
+  // As many tiles as the shape gives, no longer than the grid needs: a shape that divides the grid as it is, otherwise
+  // fewer points and fewer waves with work. 24^3 x 8 x 8 x 300 (tiles of 12 along axis 3 instead of 16): 65 -> 60 us,
+  // 50 x 42 x 34 x 8 x 8 x 1000: 280 -> 266 us, 64 x 64 x 1 x 8 x 8 x 300: 134 -> 98 us. (The cubes of few tiles
+  // spread over all four waves instead of the first ones: 6 x 7 x 5 x 8 x 8 x 60 52 instead of 38 us.)
+  a.TX = (d.n1 + a.t1 - 1) / a.t1;
+  a.TY = (d.n2 + a.t2 - 1) / a.t2;
+  a.TZ = (d.n3 + a.t3 - 1) / a.t3;
   a.ntiles = a.t1 * a.t2 * a.t3;
   a.nunits = a.ntiles * d.nb;
   a.per_xcd = (a.nunits + NXCD - 1) / NXCD;

@@ -227,7 +227,7 @@ __device__ __forceinline__ void chi_unit(const ChiArgs& a, int tile, int n, int 
   auto lane_cube = [&](int i, int& pbase) {
     const int cz = i % TZ, cy = (i / TZ) % TY, cx = i / (TZ * TY);
     pbase = (cx * PY + cy) * PZ + cz;
-    return (x0 + cx < a.n1) && (y0 + cy < a.n2) && (z0 + cz < a.n3);
+    return cx < TX && (x0 + cx < a.n1) && (y0 + cy < a.n2) && (z0 + cz < a.n3);
   };
   auto point_offset = [PY, PZ](int s) { return (s & 1) * (PY * PZ) + ((s >> 1) & 1) * PZ + (s >> 2); };
 
@@ -631,12 +631,14 @@ hipError_t chi(const tetra_desc& d, int q1, int q2, int q3, float e_fermi, const
   a.inv_de = 1.0f / d.de;
   a.V = (float)(1.0 / (24.0 * (double)d.n1 * d.n2 * d.n3));
   const TileShape sh = tile_shape(shape);
-  a.TX = sh.x;
-  a.TY = sh.y;
-  a.TZ = sh.z;
   a.t1 = (d.n1 + sh.x - 1) / sh.x;
   a.t2 = (d.n2 + sh.y - 1) / sh.y;
   a.t3 = (d.n3 + sh.z - 1) / sh.z;
+  // As many tiles as the shape gives, no longer than the grid needs: 24^3 x 12 x 12 x 300 (12 along axis 3 instead of
+  // 16) 410 -> 394 us.
+  a.TX = (d.n1 + a.t1 - 1) / a.t1;
+  a.TY = (d.n2 + a.t2 - 1) / a.t2;
+  a.TZ = (d.n3 + a.t3 - 1) / a.t3;
   a.ntiles = a.t1 * a.t2 * a.t3;
   // Workgroups per (tile, band n): more of them even out the pairs that do contribute, a few per (tile, n); each
   // takes its time to start, whether it finds a pair or not (10 ns for one of the spline pass). 64^3 x 8 x 8 x 500:
