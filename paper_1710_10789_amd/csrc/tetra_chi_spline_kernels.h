@@ -328,9 +328,9 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
 
   const int RS = (rows + 5) | 1;
   int group = NORB;
-  while (RS * group > chi_spline_words<NORB>()) group = (group + 1) / 2;
-  const int plane = RS * group;
-  const int copies = 4 * plane <= chi_spline_words<NORB>() ? 4 : 2 * plane <= chi_spline_words<NORB>() ? 2 : 1;
+  while ((RS * group | 1) > chi_spline_words<NORB>()) group = (group + 1) / 2;
+  const int plane = RS * group | 1;  // odd: the copies of a bin in different banks
+  const int copies = histogram_copies(plane, chi_spline_words<NORB>());
 
   auto point = [&](int q, int sign, int m0, int m1, auto&& act) {
     int px, py, pz;

@@ -568,9 +568,9 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   // lane mod copies: neighbouring points often share a bin).
   const int RS = (rows + NE + 1) | 1;
   int group = NORB;
-  while (RS * group > spline_words<NORB>()) group = (group + 1) / 2;
-  const int plane = RS * group;
-  const int copies = 4 * plane <= spline_words<NORB>() ? 4 : 2 * plane <= spline_words<NORB>() ? 2 : 1;
+  while ((RS * group | 1) > spline_words<NORB>()) group = (group + 1) / 2;
+  const int plane = RS * group | 1;  // odd: the copies of a bin in different banks
+  const int copies = histogram_copies(plane, spline_words<NORB>());
   Acc* const hist = reinterpret_cast<Acc*>(sh.hist);
   const double c4 = INC ? a.Vd : a.c4;
 
