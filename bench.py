@@ -269,7 +269,7 @@ def summarize_profiles(kt_dir, fetch_dir=None, write_dir=None, copy_fetch_dir=No
             lines.append(f"| `{k[:90]}` | {fe[k]:.0f} | {wr[k]:.0f} | {rd / 1e6:.2f} | {wt / 1e6:.2f} |")
             for short, pat in (("dos_forward_kernel", "dos_forward_kernel"), ("dos_backward_kernel", "dos_backward_kernel"),
                                ("dos_backward_kernel", "bwd_gather_kernel"), ("nos_kernel", "nos_kernel"),
-                               ("chi_kernel", "chi_kernel")):
+                               ("chi_kernel", "chi_kernel"), ("chi_kernel", "chi_spline_kernel")):
                 if pat in k:  # the kernels launched by one call add up (instantiations, gather pass)
                     sha = (source_shas or {}).get(short) or kernel_source_hash(short)
                     rec = traffic.setdefault(short, {"source_sha": sha, "config": (configs or {}).get(short),
@@ -542,7 +542,7 @@ def nos_record(args, torch, tetra, dev, with_oracle=True):
                    "tile": list(tetra.TILE_SHAPES[tile])},
         "ms": ms,
         "binned_updates_per_s": dense / (ms["binned"] * 1e-3),
-        "roofline": {"bound": "alu", "kernel": "nos_kernel, both precisions (bin averages; events include the zero fill)",
+        "roofline": {"bound": "alu", "kernel": "nos_kernel (bin averages; events include the zero fill)",
                      "achieved": achieved, "peak": PEAK_FP32_VALU_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_FP32_VALU_TFLOPS, "traffic": load_traffic("nos_kernel"),
                      "algorithmic_flops_per_launch": flops, "avg_launch_ms": ms["binned"]},
@@ -611,7 +611,7 @@ def chi_record(args, torch, tetra, dev, with_oracle=True):
         "data": "synthetic (seeded random 8-orbital tight-binding model; eigh on the host, untimed)",
         "config": {"workload": "chi_k64_b8_w500: 64^3 periodic k-grid, 8 bands x 8 orbitals, q = (16, 16, 0), "
                                "500 transfer energies, E_F at half filling; tetra_chi_spectral_ws (first pass of "
-                               "per-(tile, band) energy ranges, then chi_kernel)",
+                               "per-(tile, band) energy ranges, then chi_spline_kernel and chi_kernel)",
                    "dense_updates_per_pass": dense, "tile": list(tetra.TILE_SHAPES[tile])},
         "tile_ms": times,
         "kernel_source_sha": {"chi_kernel": kernel_source_hash("chi_kernel")},
@@ -632,7 +632,8 @@ def chi_record(args, torch, tetra, dev, with_oracle=True):
                            "peak": PEAK_FP32_VALU_TFLOPS, "unit": "TFLOP/s",
                            "frac": achieved / PEAK_FP32_VALU_TFLOPS, "traffic": load_traffic("chi_kernel"),
                            "algorithmic_flops_per_launch": flops, "avg_launch_ms": ms,
-                           "timed_over": "the whole call: zero fill, chi_ranges_kernel (first pass), chi_kernel"}
+                           "timed_over": "the whole call: zero fill, chi_ranges_kernel (first pass), chi_spline_kernel, "
+                                         "chi_kernel"}
         rec["error_vs_fp64_oracle"] = float(np.abs(got - ref).max() / np.abs(ref).max())
         rec["cpu_baseline"] = {"value": dense / t_or, "unit": "updates/s", "cores": cores, "kind": "oracle",
                                "sample": f"the whole workload, one pass, FP64 ({t_or:.1f} s)"}
@@ -645,7 +646,7 @@ def bench_chi(args, torch, tetra, dev):
 
 def batched_record(args, torch, tetra, dev):
     """32 independently seeded 8-orbital models, cubic grids from {24,32,48,64,96}^3 and 256..2048
-    energies, through one persistent launch captured in a HIP graph, tile shapes per problem from the
+    energies, through one launch captured in a HIP graph, tile shapes per problem from the
     autotuner."""
     from paper_1710_10789_amd import tune
 
@@ -677,7 +678,7 @@ def batched_record(args, torch, tetra, dev):
     ms_single = _time_events(torch, lambda: [tetra.dos_forward(*p, tile=t) for p, t in zip(probs, tiles)],
                              args.steps, args.warmup)
     return {
-        "metric": "tetra-band-energy updates/s, batched (32 models, one persistent graph-captured launch)",
+        "metric": "tetra-band-energy updates/s, batched (32 models, one graph-captured launch)",
         "value": dense / (ms_graph * 1e-3),
         "unit": "updates/s",
         "n_gpus": 1,
@@ -733,7 +734,7 @@ def main():
                          "x 2000, batched 32 models, number of states, susceptibility)")
     ap.add_argument("--workload", choices=["headline", "precision", "batched", "paper", "nos", "chi"], default="headline",
                     help="headline: 64^3 x 8 x 8 x 1000 fwd+bwd (the metric); precision: 128^3 x 16 x 16 x 2000 "
-                         "with FP16 weights and exact accumulation; batched: 32 models, one persistent launch; "
+                         "with FP16 weights and exact accumulation; batched: 32 models, one launch; "
                          "paper: the paper's 60 x 60 x 10 x 8 x 1024 forward, for context; nos: number of states "
                          "and bin-averaged DOS at the headline shape; chi: susceptibility spectral weight at the "
                          "headline model")

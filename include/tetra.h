@@ -88,7 +88,8 @@ enum {
   TETRA_DETERMINISTIC = 2u,
   /* Bits 8..11 select the tile shape of the forward and adjoint kernels (0 = default); an autotuner
    * picks it per problem class. Shapes are TX x TY x TZ cubes along grid axes (1, 2, 3):
-   * 0: 4x4x16, 1: 8x8x4, 2: 4x8x8, 3: 8x4x8, 4: 4x16x4, 5: 16x4x4. */
+   * 0: 4x4x16, 1: 8x8x4, 2: 4x8x8, 3: 8x4x8, 4: 4x16x4, 5: 16x4x4. The forward, batched and
+   * number-of-states kernels take tiles of 8x8x8 for 0 and up to 8 of each side of the others. */
   TETRA_TILE_MASK = 0xF00u
 };
 #define TETRA_TILE(v) (((unsigned)(v) & 0xFu) << 8)
@@ -303,17 +304,17 @@ typedef struct {
 
 /*
  * Bytes of device workspace tetra_dos_batched needs for these items (host array of n items):
- * 256 per persistent launch. Returns 0 for invalid input.
+ * 256 per launch. Returns 0 for invalid input.
  */
 size_t tetra_dos_batched_workspace(const tetra_item* items, int n, int wtype, unsigned flags);
 
 /*
- * Many independent problems (uneven grids, energy grids, band counts) through one persistent launch
- * per group of up to 32 items with the same orbital count: workgroups pull (item, band, tile) units
- * from a work counter, so problems of very different sizes share the chip. `items` is host memory
+ * Many independent problems (uneven grids, energy grids, band counts) through one launch per group
+ * of up to 32 items with the same orbital count, a workgroup per (item, band, tile) unit, so problems
+ * of very different sizes share the chip. `items` is host memory
  * read during the call (the descriptors travel as kernel arguments); `workspace` is device memory of
- * at least tetra_dos_batched_workspace() bytes (one 256-byte counter per launch), owned by the caller
- * and not used by anything else until the work on `stream` completes. Each item's dos is
+ * at least tetra_dos_batched_workspace() bytes (256 per launch, which the kernels leave alone), owned
+ * by the caller. Each item's dos is
  * overwritten. Every item uses weight type wtype (with its own w_scale for TETRA_W_F16).
  * Allocates nothing and copies nothing to the device, so a call can be captured in a HIP graph.
  * flags must be 0 (TETRA_EXACT and TETRA_DETERMINISTIC are not supported here:

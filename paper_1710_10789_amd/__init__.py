@@ -470,7 +470,7 @@ def batched_workspace_bytes(problems) -> int:
 
 
 def dos_batched(problems, *, workspace=None, out=None, tiles=None):
-    """DOS of many independent problems in one persistent launch per orbital count.
+    """DOS of many independent problems in one launch per orbital count.
 
     problems: sequence of ``(eps, w, grid, e0, de, ne)`` or ``(eps, w, grid, e0, de, ne, w_scale)``
     with the same meaning as in :func:`dos_forward`. ``workspace`` is an optional uint8 device tensor
