@@ -530,8 +530,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   const int base = uniform((int)floor(umin)), rows = uniform((int)rows_d);
   const float J = (float)rows, limit = (MODE == 2 ? kDegenerateExact : a.degenerate) * J * J * J;
 
-  // Degenerate tetrahedra: their bits at their corner points, and a queue. Corners 2 and 5 belong to all six
-  // of Table I, the other two run around them.
+  // Degenerate tetrahedra: their bits at their corner points, and a queue of those with finite corners.
   const int by_cz = small_inverse(cz), by_cy = small_inverse(cy);
   for_lanes(ncubes, [&](int c) {
     const int r = small_div(c, by_cz), iz = c - r * cz, ix = small_div(r, by_cy), iy = r - ix * cy;
@@ -539,18 +538,17 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     float f[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) f[s] = fc[(s & 1) * PY + ((s >> 1) & 1) * PZ + (s >> 2)];
-    const float d0 = fminf(f[2], f[5]), d1 = fmaxf(f[2], f[5]);
-    auto gap = [&](int i, int j) { return spline_gap(d0, d1, fminf(f[i], f[j]), fmaxf(f[i], f[j])); };
-    const float g[6] = {gap(0, 1), gap(1, 3), gap(0, 4), gap(3, 7), gap(4, 6), gap(6, 7)};
-    if (!(fminf(fminf(fminf(g[0], g[1]), fminf(g[2], g[3])), fminf(g[4], g[5])) >= limit)) {
+    uint32_t finite;
+    const uint32_t out = left_out(f, limit, finite);
+    if (out) {
 #pragma unroll
       for (int t = 0; t < 6; ++t) {
+        if (!((out >> t) & 1u)) continue;
+        if ((finite >> t) & 1u) {
+          const int at = atomicAdd(&sh.nq, 1);
+          if (at < kQueue) sh.queue[at] = (unsigned short)(c * 6 + t);
+        }
         const uint32_t slots = tet_slots(t);
-        const float top = fmaxf(d1, fmaxf(f[t == 0 || t == 2 ? 0 : t == 1 ? 1 : t == 3 ? 3 : t == 4 ? 4 : 6],
-                                          f[t == 0 ? 1 : t == 1 ? 3 : t == 2 ? 4 : t == 4 ? 6 : 7]));
-        if (g[t] >= limit || !(top < __builtin_huge_valf())) continue;
-        const int at = atomicAdd(&sh.nq, 1);
-        if (at < kQueue) sh.queue[at] = (unsigned short)(c * 6 + t);
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
           const int s = (slots >> (4 * l)) & 7;

@@ -1,0 +1,73 @@
+"""Energies at the edges of the spline kernels' rules, through the C ABI: points without a finite energy beside equal
+ones, flat tetrahedra exactly on a grid energy, a point far off the others. Against the FP64 oracle, gate 1e-5 of the
+largest value (FP32 energies and additions)."""
+import numpy as np
+import pytest
+
+import synth
+from gates import dos_err
+
+pytestmark = pytest.mark.gpu
+
+KINDS = ["dos", "exact", "batched", "nos", "binned"]
+
+
+def _both(oracle_lib, kind, eps, w, grid, e0, de, ne, flat):
+    """The oracle's result and the library's. A tetrahedron that is flat at a grid energy counts there (E_j >= E4),
+    in the oracle only above it (E_j > E1): it gets that energy one step down."""
+    import torch
+    import paper_1710_10789_amd as tetra
+
+    te, tw = torch.from_numpy(eps).cuda(), torch.from_numpy(w).cuda()
+    args = (te, tw, grid, e0, de, ne)
+    if flat is not None:
+        eps = np.where(eps == np.float32(flat), np.nextafter(np.float32(flat), np.float32(-np.inf)), eps)
+    if kind == "nos":
+        ref, got = oracle_lib.nos(eps, w, grid, e0, de, ne), tetra.nos_forward(*args)
+    elif kind == "binned":
+        ref, got = oracle_lib.dos_binned(eps, w, grid, e0, de, ne), tetra.dos_binned(*args)
+    else:
+        ref = oracle_lib.dos(eps, w, grid, e0, de, ne)
+        if kind == "batched":
+            got = tetra.dos_batched([args + (None,), args + (None,)])[1]
+        else:
+            got = tetra.dos_forward(*args, deterministic=kind == "exact")
+    return np.asarray(ref[0] if isinstance(ref, tuple) else ref), got.double().cpu().numpy()
+
+
+def _check(oracle_lib, kind, eps, w, grid, e0, de, ne, flat=None):
+    ref, got = _both(oracle_lib, kind, eps, w, grid, e0, de, ne, flat)
+    assert np.isfinite(got).all()
+    assert np.abs(ref).max() > 0.0
+    err = dos_err(got, ref)
+    print(f"[case] err {err:.2e}", flush=True)
+    assert err <= 1e-5
+
+
+def _bands(grid, nb=2, seed=3):
+    """Random energies in [0, 1] that no two points share, and positive weights."""
+    rng = np.random.default_rng(seed)
+    nk = int(np.prod(grid))
+    eps = np.stack([rng.permutation(nk) for _ in range(nb)]).astype(np.float32) / np.float32(nk)
+    return eps, rng.random((nb, 3, nk)).astype(np.float32)
+
+
+# pairs of neighbours with one energy and the point without one that their only tetrahedron of the first tile has
+TIED = [((0, 0, 0), (1, 0, 0), (0, 1, 0)), ((0, 0, 0), (0, 0, 1), (1, 0, 1)), ((0, 0, 0), (0, 1, 0), (1, 0, 0))]
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("kind", KINDS)
+def test_tie_beside_a_point_without_energy(oracle_lib, kind, bad):
+    grid, ne = (16, 16, 16), 120
+    for a, b, c in TIED:
+        eps, w = _bands(grid)
+        cube = eps.reshape(2, *grid)
+        cube[:, b[0], b[1], b[2]] = cube[:, a[0], a[1], a[2]]
+        for x in range(2):  # the whole neighbourhood but the pair
+            for y in range(2):
+                for z in range(2):
+                    if (x, y, z) not in (a, b) and ((x, y, z) == c or bad == np.inf):
+                        cube[:, x, y, z] = bad
+        print(f"[case] {kind} {bad} {a} {b}", flush=True)
+        _check(oracle_lib, kind, eps, w, grid, -0.02, float(np.float32(1.04 / (ne - 1))), ne)

@@ -1,0 +1,33 @@
+"""What the spline form leaves out (``left_out`` in ``tetra_spline.h``), built for the host with g++: a pair of equal
+energies and points without one in every placement of a block of cubes. No GPU needed.
+
+Bound: as for the spline form itself (a kept tetrahedron loses 2e-4 of its own density at worst, a tenth of that in
+the sum over a block)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def _run(tmp_path, oracle_lib, name):
+    if shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"):
+        pytest.skip("needs g++ and the ROCm headers")
+    exe = str(tmp_path / name)
+    odir = os.path.dirname(oracle_lib.build())
+    res = subprocess.run(["g++", "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+                          os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1710_10789_amd", "csrc"),
+                          os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe, "-L", odir,
+                          "-ltetra_oracle", f"-Wl,-rpath,{odir}"], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stderr
+    print(out.stdout)
+    return {line.split()[0]: line.split()[1:] for line in out.stdout.strip().split("\n")}
+
+
+def test_ties_beside_points_without_energy(tmp_path, oracle_lib):
+    placements, bad, err = _run(tmp_path, oracle_lib, "spline_edges_check")["ties"]
+    assert int(placements) > 10000 and int(bad) == 0 and float(err) <= 2e-5
