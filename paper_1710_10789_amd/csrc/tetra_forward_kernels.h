@@ -524,7 +524,10 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   }
   // Rows of the sums: from the first grid energy at or above the lowest knot (below the grid's first
   // energy too) to the last one below the highest (the first at or above it for the increments).
-  const double rows_d = INC ? fmin(ceil(umax), (double)(a.ne - 1)) + 1.0 - floor(umin)
+  auto index = [&](float e, bool above, double lo, double top) {  // INC
+    return energy_index(e, e0, (double)a.de, inv_de, joff, above, lo, top);
+  };
+  const double rows_d = INC ? fmin(fmax(ceil(umax), index(emax, false, -1.0, (double)a.ne)), (double)(a.ne - 1)) + 1.0 - floor(umin)
                             : fmin(ceil(umax), (double)a.ne) - floor(umin);
   if (!(rows_d + NE + 2 <= (double)spline_words<NORB>())) return false;
   const int base = uniform((int)floor(umin)), rows = uniform((int)rows_d);
@@ -646,13 +649,12 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     };
     if constexpr (INC) {
       const NosVolumes c = nos_volumes(e);
-      const double u1 = (c.e[0] - e0) * inv_de - joff, u4 = (c.e[3] - e0) * inv_de - joff;
-      const int js = (int)fmin(ceil(u4), (double)(base + rows - 1)), ja = min((int)floor(u1) + 1, js);
+      const int full = (int)index(e[3], false, base, (double)a.ne), js = min(full, base + rows - 1);
+      const int ja = min((int)index(e[0], true, base, (double)a.ne), js);
       for (int j = ja + (i16 & 15); j <= js; j += 16) {
-        const double E = e0 + (j + joff) * (double)a.de;
-        double w0[4], w1[4];
-        corner_nos(c, 1.0, E - (double)a.de, w0);
-        corner_nos(c, 1.0, E, w1);
+        double w0[4] = {0.0, 0.0, 0.0, 0.0}, w1[4] = {1.0, 1.0, 1.0, 1.0};
+        if (j > ja) corner_nos(c, 1.0, e0 + (j - 1 + joff) * (double)a.de, w0);
+        if (j < full) corner_nos(c, 1.0, e0 + (j + joff) * (double)a.de, w1);
         put(j, w1[0] - w0[0], w1[1] - w0[1], w1[2] - w0[2], w1[3] - w0[3]);
       }
     } else {

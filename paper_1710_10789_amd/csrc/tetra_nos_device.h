@@ -115,6 +115,25 @@ __host__ __device__ __forceinline__ void corner_nos(const NosVolumes& c, double 
   }
 }
 
+// The first grid index j with E_j at or above (above = false) or above (true) e, on E_j = e0 + (j + joff) de: the
+// rounded quotient, put right by the sign of e - E_j, which the fused product gives exactly (e - e0 of two FP32
+// values and the product's 46 bits are exact). Without it a flat tetrahedron on a grid energy whose quotient
+// rounds up, such as 32.8125 / 4.6875, is full one energy before its step is looked for. Kept inside [lo, top].
+__host__ __device__ __forceinline__ double energy_index(float e, double e0, double de, double inv_de, double joff,
+                                                      bool above, double lo, double top) {
+  const double x = (double)e - e0, u = x * inv_de - joff;
+  if (!(u > lo)) return lo;
+  if (!(u < top)) return top;
+  double j = ceil(u);
+  auto past = [&](double i) {
+    const double r = __builtin_fma(-(i + joff), de, x);  // e - E_i
+    return above ? r < 0.0 : r <= 0.0;
+  };
+  if (!past(j)) j += 1.0;
+  else if (past(j - 1.0)) j -= 1.0;
+  return fmin(j, top);
+}
+
 // FP64 constants of one tetrahedron-band.
 struct NosSetup {
   double x0, z0, y0;  // grid index 0 in the local frames: E_0 - E1, E_0 - E2, E4 - E_0

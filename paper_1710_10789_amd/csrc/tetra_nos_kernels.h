@@ -85,10 +85,7 @@ __device__ __forceinline__ void general_nos(const FwdArgs& a, int unit, NosGener
   if (!(emin <= emax)) return;  // no finite energy
   const double e0 = a.e0, de = a.de, inv_de = a.inv_ded, joff = a.joff, top = (double)(a.ne - 1);
   // grid index of the first energy above (shift 1) or at or above (shift 0) an energy, kept inside the grid
-  auto index = [&](float e, bool above) {
-    const double u = ((double)e - e0) * inv_de - joff;
-    return (int)fmin(fmax(above ? floor(u) + 1.0 : ceil(u), 0.0), top + 1.0);
-  };
+  auto index = [&](float e, bool above) { return (int)energy_index(e, e0, de, inv_de, joff, above, 0.0, top + 1.0); };
   const int J0 = uniform(index(emin, false)), J1 = min(uniform(index(emax, false)), a.ne - 1);
   for (int c0 = J0; c0 <= J1; c0 += RS) {
     const int c1 = min(c0 + RS - 1, J1), L = c1 - c0 + 1;
@@ -114,11 +111,11 @@ __device__ __forceinline__ void general_nos(const FwdArgs& a, int unit, NosGener
         if (ja > c1 || j1 < c0) continue;
         const NosVolumes v = nos_volumes(e);
         const int j0 = max(ja, c0);
-        double prev[4] = {0.0, 0.0, 0.0, 0.0};
-        if (j0 > 0) corner_nos(v, a.Vd, e0 + (j0 - 1 + joff) * de, prev);
+        double prev[4] = {0.0, 0.0, 0.0, 0.0};  // nothing below the first increment, everything from the last one on
+        if (j0 > ja) corner_nos(v, a.Vd, e0 + (j0 - 1 + joff) * de, prev);
         for (int j = j0; j <= j1; ++j) {
-          double cur[4];
-          corner_nos(v, a.Vd, e0 + (j + joff) * de, cur);
+          double cur[4] = {a.Vd, a.Vd, a.Vd, a.Vd};
+          if (j < js) corner_nos(v, a.Vd, e0 + (j + joff) * de, cur);
           const double g0 = cur[0] - prev[0], g1 = cur[1] - prev[1], g2 = cur[2] - prev[2], g3 = cur[3] - prev[3];
 #pragma unroll 1
           for (int m = 0; m < NORB; ++m) {

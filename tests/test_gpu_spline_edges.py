@@ -71,3 +71,26 @@ def test_tie_beside_a_point_without_energy(oracle_lib, kind, bad):
                         cube[:, x, y, z] = bad
         print(f"[case] {kind} {bad} {a} {b}", flush=True)
         _check(oracle_lib, kind, eps, w, grid, -0.02, float(np.float32(1.04 / (ne - 1))), ne)
+
+
+def _flat(some, e, grid=(16, 9, 8), nb=2):
+    """Bands around e, all of them flat there or only a block of 4 x 4 x 4 points."""
+    eps, w = _bands(grid, nb)
+    eps = (np.float32(e) * (np.float32(0.6) + np.float32(0.8) * eps)).astype(np.float32)
+    if some:
+        eps.reshape(nb, *grid)[:, 2:6, 3:7, 1:5] = e
+    else:
+        eps[:] = e
+    return eps, w, grid
+
+
+# (e - e0) / de comes out above the whole number that it is for 7 x 4.6875 and 15 x 1.171875
+@pytest.mark.parametrize("some", [True, False])
+@pytest.mark.parametrize("kind", ["nos", "binned"])
+@pytest.mark.parametrize("step,j", [(4.6875, 7), (0.25, 6), (0.3, 4), (1.171875, 15)])
+def test_flat_on_an_inner_grid_energy(oracle_lib, kind, some, step, j):
+    de = float(np.float32(step))
+    e = float(np.float32(j * de))
+    eps, w, grid = _flat(some, e)
+    print(f"[case] {kind} some={some} de {de} E {e}", flush=True)
+    _check(oracle_lib, kind, eps, w, grid, 0.5 * de if kind == "binned" else 0.0, de, 3 * j, flat=e)

@@ -1,5 +1,6 @@
 """What the spline form leaves out (``left_out`` in ``tetra_spline.h``), built for the host with g++: a pair of equal
-energies and points without one in every placement of a block of cubes. No GPU needed.
+energies and points without one in every placement of a block of cubes; and the number of states' grid index and
+volumes (``tetra_nos_device.h``). No GPU needed.
 
 Bound: as for the spline form itself (a kept tetrahedron loses 2e-4 of its own density at worst, a tenth of that in
 the sum over a block)."""
@@ -31,3 +32,11 @@ def _run(tmp_path, oracle_lib, name):
 def test_ties_beside_points_without_energy(tmp_path, oracle_lib):
     placements, bad, err = _run(tmp_path, oracle_lib, "spline_edges_check")["ties"]
     assert int(placements) > 10000 and int(bad) == 0 and float(err) <= 2e-5
+
+
+def test_number_of_states_index_and_volumes(tmp_path, oracle_lib):
+    """No index may be wrong; the volume form has no cancellation and the oracle's, in FP64 as well, a few digits of
+    it (1e-16 times the inverse of the smallest of 20,000 random gaps, about 1e-5)."""
+    rows = _run(tmp_path, oracle_lib, "nos_index_check")
+    assert int(rows["index"][0]) == 40000 and int(rows["index"][1]) == 0
+    assert float(rows["volumes"][0]) <= 1e-10
