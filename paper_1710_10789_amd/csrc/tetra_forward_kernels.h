@@ -491,7 +491,11 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   emax = uniform(emax);
   if (!(emin <= emax)) return true;  // no finite energy
   const double umin = ((double)emin - e0) * inv_de - joff, umax = ((double)emax - e0) * inv_de - joff;
-  if (!(umin < (double)(a.ne - 1))) return true;  // above the energy grid
+  auto index = [&](float e, bool above, double lo, double top) {  // INC
+    return energy_index(e, e0, (double)a.de, inv_de, joff, above, lo, top);
+  };
+  // above the energy grid (a flat tetrahedron on its last energy has all its states there)
+  if (INC ? index(emin, false, -1.0, (double)a.ne) > (double)(a.ne - 1) : !(umin < (double)(a.ne - 1))) return true;
   if (!(uniform(bmax) < 3.0e38f)) return false;
   if (!(umax > 0.0)) {  // below it
     if (INC && a.shift == 0) {
@@ -524,9 +528,6 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   }
   // Rows of the sums: from the first grid energy at or above the lowest knot (below the grid's first
   // energy too) to the last one below the highest (the first at or above it for the increments).
-  auto index = [&](float e, bool above, double lo, double top) {  // INC
-    return energy_index(e, e0, (double)a.de, inv_de, joff, above, lo, top);
-  };
   const double rows_d = INC ? fmin(fmax(ceil(umax), index(emax, false, -1.0, (double)a.ne)), (double)(a.ne - 1)) + 1.0 - floor(umin)
                             : fmin(ceil(umax), (double)a.ne) - floor(umin);
   if (!(rows_d + NE + 2 <= (double)spline_words<NORB>())) return false;

@@ -94,3 +94,16 @@ def test_flat_on_an_inner_grid_energy(oracle_lib, kind, some, step, j):
     eps, w, grid = _flat(some, e)
     print(f"[case] {kind} some={some} de {de} E {e}", flush=True)
     _check(oracle_lib, kind, eps, w, grid, 0.5 * de if kind == "binned" else 0.0, de, 3 * j, flat=e)
+
+
+@pytest.mark.parametrize("some", [True, False])
+@pytest.mark.parametrize("kind", ["nos", "binned"])
+@pytest.mark.parametrize("ne", [1, 2, 7])
+def test_flat_on_the_last_grid_energy(oracle_lib, kind, some, ne):
+    """The last energy (the upper edge of the last bin) is exactly that of the flat tetrahedra: they count there."""
+    de, e = 0.25, 2.0
+    eps, w, grid = _flat(some, e)
+    eps = np.maximum(eps, np.float32(e)) if some else eps  # nothing below it, so that nothing else hides them
+    e0 = e - (ne - 1) * de - (0.5 * de if kind == "binned" else 0.0)
+    print(f"[case] {kind} some={some} ne {ne}", flush=True)
+    _check(oracle_lib, kind, eps, w, grid, e0, de, ne, flat=e)
