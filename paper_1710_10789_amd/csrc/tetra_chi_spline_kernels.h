@@ -224,11 +224,11 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
     const uint32_t plus = taken & ~minus;
     uint32_t bits = (plus ? 0x40u : 0u) | (minus ? 0x4000u : 0u) | (~plus & 0x3fu) | (~minus & 0x3fu) << 8;
     if (taken) atomicOr(&sh.signs, (int)(plus != 0u) | (int)(minus != 0u) << 1);
-    const float lo = fminf(d8[2], d8[5]) * a.inv_de, hi = fmaxf(d8[2], d8[5]) * a.inv_de;
+    const float lo = fminf(d8[2], d8[5]), hi = fmaxf(d8[2], d8[5]);
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
-      const float x = d8[I[t][0]] * a.inv_de, y = d8[I[t][1]] * a.inv_de;
-      if (!(spline_gap(lo, hi, fminf(x, y), fmaxf(x, y)) >= limit) && ((taken >> t) & 1u)) {
+      const float x = d8[I[t][0]], y = d8[I[t][1]];
+      if (!(spline_gap(lo, hi, fminf(x, y), fmaxf(x, y), a.inv_de) >= limit) && ((taken >> t) & 1u)) {
         const int at = atomicAdd(&sh.nq, 1);
         if (at < kQueue) sh.queue[at] = (unsigned short)(tid * 6 + t);
         bits |= 0x101u << t;

@@ -358,7 +358,7 @@ __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, General
 template <int NORB>
 struct SplineFixed {
   double u[kKnotPad];  // knots: energies in grid steps
-  float f[NP];         // the same from the tile's first point, for the search for degenerate tetrahedra
+  float f[NP];         // the energies, for the search for degenerate tetrahedra; infinite where not finite
   float wlo[kWeightPad];
   float w[NP * NORB];
   float whi[kWeightPad];
@@ -430,8 +430,6 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       for (int m = 0; m < NORB; ++m) ahead_w[i][m] = load_at(w_n + (int64_t)m * nk, k);
     }
   }
-  float first = eps_n[((int64_t)x0 * a.n2 + y0) * a.n3 + z0];
-  first = __builtin_isfinite(first) ? first : 0.0f;
   for_lanes(kKnotPad, [&](int i) { sh.u[i] = kFarKnot; });
   for_lanes(kWeightPad, [&](int i) { sh.wlo[i] = sh.whi[i] = 0.0f; });
   for_lanes(NP, [&](int i) { sh.skip[i] = 0u; });
@@ -445,7 +443,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     split(q, px, py, pz);
     const int p = px * PY + py * PZ + pz;
     const bool finite = __builtin_isfinite(e);
-    sh.f[p] = finite ? (e - first) * a.inv_de : __builtin_huge_valf();
+    sh.f[p] = finite ? e : __builtin_huge_valf();
     if (finite) {
       sh.u[kKnotMargin + px * SY + py * SZ + pz] = ((double)e - e0) * inv_de - joff;
       lmin = fminf(lmin, e);
@@ -543,7 +541,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
 #pragma unroll
     for (int s = 0; s < 8; ++s) f[s] = fc[(s & 1) * PY + ((s >> 1) & 1) * PZ + (s >> 2)];
     uint32_t finite;
-    const uint32_t out = left_out(f, limit, finite);
+    const uint32_t out = left_out(f, limit, finite, a.inv_de);
     if (out) {
 #pragma unroll
       for (int t = 0; t < 6; ++t) {

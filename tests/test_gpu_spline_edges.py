@@ -107,3 +107,19 @@ def test_flat_on_the_last_grid_energy(oracle_lib, kind, some, ne):
     e0 = e - (ne - 1) * de - (0.5 * de if kind == "binned" else 0.0)
     print(f"[case] {kind} some={some} ne {ne}", flush=True)
     _check(oracle_lib, kind, eps, w, grid, e0, de, ne, flat=e)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_a_point_far_off_the_others(oracle_lib, kind):
+    """One energy of another scale on a tile's first point does not coarsen the search for nearly equal energies."""
+    grid, ne = (16, 16, 16), 1000
+    eps, w = _bands(grid)
+    cube = eps.reshape(2, *grid)
+    # neighbours one step of FP32 apart, on either side of where their difference from 3000 rounds up
+    low = np.float32((4 * np.arange(2 * 4 * 4 * 4).reshape(2, 4, 4, 4) % 2048 * 4 + 1) / 8192)
+    cube[:, 1::4, 1::4, 1::4] = low
+    cube[:, 1::4, 1::4, 2::4] = np.nextafter(low, np.float32(2.0))
+    for far in (3.0e3, 1.0e30):
+        cube[:, ::8, ::8, ::8] = far
+        print(f"[case] {kind} {far}", flush=True)
+        _check(oracle_lib, kind, eps, w, grid, -0.02, float(np.float32(1.04 / (ne - 1))), ne)
