@@ -311,9 +311,10 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
           double* h = &sh.hist[m0 * chunk + j - c0];
 #pragma unroll
           for (int m = 0; m < G; ++m)
-            if (m0 + m < NORB)
-              unsafeAtomicAdd(&h[m * chunk],
-                              (double)(g[0] * wt[0][m] + g[1] * wt[1][m] + g[2] * wt[2][m] + g[3] * wt[3][m]));
+            if (m0 + m < NORB) {
+              const float v = g[0] * wt[0][m] + g[1] * wt[1][m] + g[2] * wt[2][m] + g[3] * wt[3][m];
+              if (v == v) unsafeAtomicAdd(&h[m * chunk], (double)v);  // a weight that is no number adds nothing
+            }
         });
       });
       __syncthreads();

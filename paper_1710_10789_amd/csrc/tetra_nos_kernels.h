@@ -120,7 +120,8 @@ __device__ __forceinline__ void general_nos(const FwdArgs& a, int unit, NosGener
 #pragma unroll 1
           for (int m = 0; m < NORB; ++m) {
             const float* w = sh.w + m * NP;
-            unsafeAtomicAdd(&sh.hist[m * RS + j - c0], g0 * w[pt[0]] + g1 * w[pt[1]] + g2 * w[pt[2]] + g3 * w[pt[3]]);
+            const double v = g0 * w[pt[0]] + g1 * w[pt[1]] + g2 * w[pt[2]] + g3 * w[pt[3]];
+            if (v == v) unsafeAtomicAdd(&sh.hist[m * RS + j - c0], v);  // a weight that is no number adds nothing
           }
 #pragma unroll
           for (int l = 0; l < 4; ++l) prev[l] = cur[l];

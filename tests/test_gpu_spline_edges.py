@@ -123,3 +123,38 @@ def test_a_point_far_off_the_others(oracle_lib, kind):
         cube[:, ::8, ::8, ::8] = far
         print(f"[case] {kind} {far}", flush=True)
         _check(oracle_lib, kind, eps, w, grid, -0.02, float(np.float32(1.04 / (ne - 1))), ne)
+
+
+@pytest.mark.parametrize("kind", ["dos", "nos", "binned", "chi"])
+def test_a_weight_that_is_no_number_adds_nothing(oracle_lib, kind):
+    """It takes its tetrahedra out of its own orbital and leaves the others alone."""
+    import torch
+    import paper_1710_10789_amd as tetra
+
+    grid, nb, ne = (12, 9, 8), 3, 90
+    eps, w = synth.band_structure(nb, 10, grid)
+    w = np.abs(w) + np.float32(0.05)
+    bad, orb = 3 * 72 + 5 * 8 + 4, 1
+    gone = eps.copy()
+    gone[1, bad] = np.nan
+    lo, hi = float(eps.min()), float(eps.max())
+    e0, de = float(np.float32(lo - 0.01)), float(np.float32((hi - lo) * 1.05 / (ne - 1)))
+    if kind == "chi":
+        ef, q = float(np.float32(np.median(eps))), (4, 2, 0)
+        f = lambda e, b: oracle_lib.chi(e, b, grid, q, ef, 0.0, de, ne)  # noqa: E731
+    else:
+        name = {"dos": "dos", "nos": "nos", "binned": "dos_binned"}[kind]
+        f = lambda e, b: getattr(oracle_lib, name)(e, b, grid, e0, de, ne)  # noqa: E731
+    ref, without = (r[0] if isinstance(r, tuple) else r for r in (f(eps, w), f(gone, w)))
+    ref[:, orb] = without[:, orb]
+    w[1, orb, bad] = np.nan
+    te, tw = torch.from_numpy(eps).cuda(), torch.from_numpy(w).cuda()
+    if kind == "chi":
+        got = tetra.chi_spectral(te, tw, grid, q, ef, 0.0, de, ne)
+    else:
+        got = {"dos": tetra.dos_forward, "nos": tetra.nos_forward, "binned": tetra.dos_binned}[kind](te, tw, grid, e0, de, ne)
+    got = got.double().cpu().numpy()
+    assert np.isfinite(got).all()
+    err = dos_err(got, ref)
+    print(f"[case] {kind} err {err:.2e}", flush=True)
+    assert err <= 1e-5
