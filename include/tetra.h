@@ -86,10 +86,10 @@ enum {
    * is deterministic as well. The atomic path of tetra_dos_backward, tetra_dos_batched and the
    * number-of-states calls do not offer it (TETRA_ERR_UNSUPPORTED). */
   TETRA_DETERMINISTIC = 2u,
-  /* Bits 8..11 select the tile shape of the forward and adjoint kernels (0 = default); an autotuner
+  /* Bits 8..11 select the tile shape of the adjoint and susceptibility kernels (0 = default); an autotuner
    * picks it per problem class. Shapes are TX x TY x TZ cubes along grid axes (1, 2, 3):
    * 0: 4x4x16, 1: 8x8x4, 2: 4x8x8, 3: 8x4x8, 4: 4x16x4, 5: 16x4x4. The forward, batched and
-   * number-of-states kernels take tiles of 8x8x8 for 0 and up to 8 of each side of the others. */
+   * number-of-states kernels accept the same values and take tiles of 8x8x8 for all of them. */
   TETRA_TILE_MASK = 0xF00u
 };
 #define TETRA_TILE(v) (((unsigned)(v) & 0xFu) << 8)

@@ -4,7 +4,6 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
-#include <vector>
 
 #include "tetra_internal.h"
 
@@ -68,7 +67,7 @@ tetra_status tetra_dos_forward_ws(const tetra_desc* d, const float* eps, const v
   const bool exact = (flags & (TETRA_EXACT | TETRA_DETERMINISTIC)) != 0;
   if (exact && (!workspace || ws_bytes < tetra::forward_exact_scratch_bytes(*d))) return TETRA_ERR_WORKSPACE;
   return hip_status(tetra::forward(*d, eps, w, wtype, scale_of(wtype, w_scale), dos, exact ? workspace : nullptr,
-                                   shape, (hipStream_t)stream));
+                                   (hipStream_t)stream));
 }
 
 tetra_status tetra_dos_forward(const tetra_desc* d, const float* eps, const void* w, int wtype,
@@ -130,7 +129,7 @@ tetra_status tetra_dos_forward_noalloc(const tetra_desc* d, const float* eps, co
     if (e != hipSuccess) return hip_status(e);
   }
   return hip_status(
-      tetra::forward(*d, eps, w, wtype, scale_of(wtype, w_scale), dos, ws, shape, (hipStream_t)stream));
+      tetra::forward(*d, eps, w, wtype, scale_of(wtype, w_scale), dos, ws, (hipStream_t)stream));
 }
 
 tetra_status tetra_pack_f16(int nb, int norb, int nk, const float* w, void* w16, float* w_scale, void* stream) {
@@ -184,7 +183,7 @@ tetra_status nos_entry(const tetra_desc* d, const float* eps, const void* w, int
   const int shape = (int)((flags & TETRA_TILE_MASK) >> 8);
   if (shape >= tetra::kTileShapes) return TETRA_ERR_ARG;
   if (flags & (TETRA_EXACT | TETRA_DETERMINISTIC)) return TETRA_ERR_UNSUPPORTED;
-  return hip_status(tetra::nos(*d, eps, w, wtype, scale_of(wtype, w_scale), out, binned, shape, (hipStream_t)stream));
+  return hip_status(tetra::nos(*d, eps, w, wtype, scale_of(wtype, w_scale), out, binned, (hipStream_t)stream));
 }
 
 }  // namespace
@@ -256,9 +255,7 @@ tetra_status tetra_dos_batched(const tetra_item* items, int n, int wtype, unsign
   }
   if (flags & (TETRA_EXACT | TETRA_DETERMINISTIC)) return TETRA_ERR_UNSUPPORTED;
   if (!workspace || ws_bytes < 256 * tetra::batched_launches(items, n)) return TETRA_ERR_WORKSPACE;
-  std::vector<int> shapes(n);
-  for (int i = 0; i < n; ++i) shapes[i] = items[i].tile;
-  return hip_status(tetra::batched(items, shapes.data(), n, wtype, (hipStream_t)stream));
+  return hip_status(tetra::batched(items, n, wtype, (hipStream_t)stream));
 }
 
 const char* tetra_status_string(int status) {

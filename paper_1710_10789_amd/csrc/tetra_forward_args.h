@@ -69,9 +69,8 @@ struct BatchArgs {
 };
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments");
 
-// The arguments that do not depend on the kind of sum (shape: TETRA_TILE_* index).
-FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
-                     int shape);
+// The arguments that do not depend on the kind of sum.
+FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos);
 
 // Defined per orbital count in tetra_forward_inst*.hip.
 template <int NORB>

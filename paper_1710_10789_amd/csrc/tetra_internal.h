@@ -11,8 +11,8 @@ namespace tetra {
 constexpr int kMaxBatch = 32;  // problems per batched launch
 
 // Tile shapes (cubes along grid axes 1, 2, 3): one lane per cube, kTileCubes lanes per workgroup. Shape 0 is
-// the default; the others are for the autotuner. (The forward takes tiles of 8 x 8 x 8 cubes for shape 0
-// and each side up to 8 of the others.)
+// the default; the others are for the autotuner. (The adjoint's and the susceptibility's; the forward and the
+// number of states take tiles of 8 x 8 x 8 cubes for every shape.)
 constexpr int kTileCubes = 256;
 constexpr int kTileShapes = 6;
 struct TileShape {
@@ -31,18 +31,18 @@ hipError_t fill_zero(float* p, int64_t n, hipStream_t s);
 // complex amplitudes (float2). exact_scratch (or null) is device memory of
 // forward_exact_scratch_bytes(d) for the exact cross-workgroup accumulation.
 hipError_t forward(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
-                   void* exact_scratch, int shape, hipStream_t s);
+                   void* exact_scratch, hipStream_t s);
 // Batched forward: items grouped by orbital count, up to kMaxBatch per launch (the ABI asks for 256 bytes
 // of workspace per launch; the kernels use none).
 size_t batched_launches(const tetra_item* items, int n);
-hipError_t batched(const tetra_item* items, const int* shapes, int n, int wtype, hipStream_t s);
+hipError_t batched(const tetra_item* items, int n, int wtype, hipStream_t s);
 // Exact mode of the forward: 256 bytes (the largest bound exponent), then ne*norb 64-bit sums.
 inline size_t forward_exact_scratch_bytes(const tetra_desc& d) { return 256 + 8 * (size_t)d.ne * d.norb; }
 // FP16 weights with a per-band power-of-two scale: w [nb][per_band] -> w16, w_scale [nb].
 hipError_t pack_f16(int nb, int64_t per_band, const float* w, void* w16, float* w_scale, hipStream_t s);
 // Number of states (binned = false) or bin-averaged DOS (binned = true) into out[ne][norb].
 hipError_t nos(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* out,
-               bool binned, int shape, hipStream_t s);
+               bool binned, hipStream_t s);
 // grad_w is [nb][norb][nk] floats, or [nb][norb][nk][2] for complex amplitudes. With a workspace of
 // backward_workspace_bytes(d, shape) bytes (non-zero only where the grid sides are multiples of the
 // tile's, with more than one tile per axis), tile-boundary points take the two-phase output; with

@@ -158,3 +158,16 @@ def test_a_weight_that_is_no_number_adds_nothing(oracle_lib, kind):
     err = dos_err(got, ref)
     print(f"[case] {kind} err {err:.2e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("tile", range(1, 6))
+def test_tile_ids_take_the_same_tiles(tile):
+    """The forward's tiles are the same for every id: so are the exact mode's sums, bit for bit."""
+    import torch
+    import paper_1710_10789_amd as tetra
+
+    grid, ne = (17, 16, 24), 700
+    eps, w = (torch.from_numpy(x).cuda() for x in _bands(grid))
+    args = (eps, w, grid, -0.02, float(np.float32(1.04 / (ne - 1))), ne)
+    ref = tetra.dos_forward(*args, deterministic=True)
+    assert torch.equal(ref, tetra.dos_forward(*args, deterministic=True, tile=tile))
