@@ -92,7 +92,7 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
   const int NT = blockDim.x, NW = NT >> 6;
   const int64_t nk = (int64_t)a.n1 * a.n2 * a.n3;
   const float *eps_n = a.eps + (int64_t)n * nk, *eps_p = a.eps + (int64_t)n2 * nk;
-  const double e0 = a.e0, inv_de = a.inv_ded;
+  const double e0 = a.e0d, inv_de = a.inv_ded;
   auto split = [&](int q, int& px, int& py, int& pz) {
     const int r = small_div(q, by_qz);
     pz = q - r * qz;
@@ -145,7 +145,7 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
 
   // A cube's tetrahedra: which take part (whole, not flat, not off the energy grid) and which of them count
   // negatively; d of the corners. Corners 2 and 5 belong to all six of Table I, the other two run around them.
-  const float elast = (float)(e0 + (double)(a.ne - 1) * (double)a.de);
+  const float elast = (float)(e0 + (a.ned - 1.0) * a.ded);
   constexpr int I[6][2] = {{0, 1}, {1, 3}, {0, 4}, {3, 7}, {4, 6}, {6, 7}};
   auto cube = [&](int i, int& ix, int& iy, int& iz) {
     const int r = small_div(i, by_cz);
@@ -212,11 +212,11 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
 
   // Rows of the sums: from the first grid energy at or above the lowest knot to the last one below the highest.
   const double umin = ((double)dmin - e0) * inv_de, umax = ((double)dmax - e0) * inv_de;
-  const double rows_d = fmin(ceil(umax), (double)a.ne) - floor(umin);
+  const double rows_d = fmin(ceil(umax), a.ned) - floor(umin);
   bool direct = !(rows_d + 6.0 <= (double)chi_spline_words<NORB>());
   const int base = direct ? 0 : uniform((int)floor(umin)), rows = direct ? 1 : uniform((int)rows_d);
-  const int first = uniform((int)fmin(fmax(floor(umin), 0.0), (double)a.ne));  // energy by energy
-  const int last = uniform((int)fmin(ceil(umax), (double)(a.ne - 1)));
+  const int first = uniform((int)fmin(fmax(floor(umin), 0.0), a.ned));  // energy by energy
+  const int last = uniform((int)fmin(ceil(umax), (a.ned - 1.0)));
   const float J = (float)rows, limit = a.degenerate * J * J * J;
 
   // The cube's word; degenerate tetrahedra into the queue.
@@ -224,11 +224,11 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
     const uint32_t plus = taken & ~minus;
     uint32_t bits = (plus ? 0x40u : 0u) | (minus ? 0x4000u : 0u) | (~plus & 0x3fu) | (~minus & 0x3fu) << 8;
     if (taken) atomicOr(&sh.signs, (int)(plus != 0u) | (int)(minus != 0u) << 1);
-    const float lo = fminf(d8[2], d8[5]), hi = fmaxf(d8[2], d8[5]);
+    const float lo = fminf(d8[2], d8[5]) * a.unit, hi = fmaxf(d8[2], d8[5]) * a.unit;
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
-      const float x = d8[I[t][0]], y = d8[I[t][1]];
-      if (!(spline_gap(lo, hi, fminf(x, y), fmaxf(x, y), a.inv_de) >= limit) && ((taken >> t) & 1u)) {
+      const float x = d8[I[t][0]] * a.unit, y = d8[I[t][1]] * a.unit;
+      if (!(spline_gap(lo, hi, fminf(x, y), fmaxf(x, y), a.width) >= limit) && ((taken >> t) & 1u)) {
         const int at = atomicAdd(&sh.nq, 1);
         if (at < kQueue) sh.queue[at] = (unsigned short)(tid * 6 + t);
         bits |= 0x101u << t;

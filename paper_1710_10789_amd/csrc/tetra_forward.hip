@@ -45,6 +45,9 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
   a.e0 = d.e0;
   a.de = d.de;
   a.inv_de = 1.0f / d.de;
+  a.e0d = d.e0;
+  a.ded = d.de;
+  a.ned = d.ne;
   const double V = 1.0 / (24.0 * (double)d.n1 * d.n2 * d.n3);  // V_T / (4 V_G)
   a.V = (float)V;
   a.inv_ded = 1.0 / (double)d.de;
@@ -54,7 +57,11 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
   // the error of the sum (error of one ~ limit^-3/4, number^-1/2). 64^3 x 8 x 8 x 1000: 0.174 against
   // 0.184 ms with the same error, 3.0e-7, against FP64; a hundredth would raise it to 4.2e-7.
   const double points = (double)d.n1 * d.n2 * d.n3 * d.nb;
-  a.degenerate = kDegenerate / (float)std::min(10.0, std::max(1.0, std::pow(points / 32768.0, 2.0 / 3.0)));
+  a.unit = step_unit(d.de);
+  a.width = d.de * a.unit;
+  const float width4 = a.width * a.width * a.width * a.width;
+  a.degenerate = kDegenerate / (float)std::min(10.0, std::max(1.0, std::pow(points / 32768.0, 2.0 / 3.0))) * width4;
+  a.degenerate_exact = kDegenerateExact * width4;
   a.joff = 0.0;
   a.Vd = V;
   a.out_scale = 1.0;
@@ -69,7 +76,7 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
     r[i] = n[i] % t[i];
     lanes *= s[i] + (r[i] > 0);
   }
-  a.lanes = (lanes + 63) / 64 * 64;
+  a.lanes = std::max((lanes + 63) / 64 * 64, 256);  // small and flat tiles: more lanes than cubes for the rest
   a.t2 = t[1];
   a.t3 = t[2];
   a.s1 = s[0];

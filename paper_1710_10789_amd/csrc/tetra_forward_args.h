@@ -30,8 +30,11 @@ struct FwdArgs {
   int wtype;                 // TETRA_W_* of w
   int n1, n2, n3, ne;
   float e0, de, inv_de, V;
-  float degenerate;    // limit of a degenerate tetrahedron (tetra_spline.h), times rows^3
-  double inv_ded, c4;  // 1/de and 4 V_T/(4 V_G) / de in FP64
+  float unit, width;   // a power of two and a grid step in energies times it (tetra_spline.h)
+  float degenerate;    // limit of a degenerate tetrahedron (tetra_spline.h) in these, times rows^3
+  float degenerate_exact;  // the same of the exact mode
+  double e0d, ded, ned;  // e0, de and ne in FP64 (from the arguments straight into scalar registers)
+  double inv_ded, c4;    // 1/de and 4 V_T/(4 V_G) / de in FP64
   int t2, t3;          // tiles along axes 2 and 3
   int s1, s2, s3;      // cubes of the smaller tiles along each axis; the first r1, r2, r3 have one more
   int r1, r2, r3;

@@ -6,28 +6,21 @@
 //
 // Work decomposition: one workgroup per (tile of at most 8 x 8 x 8 cubes, band). The tile's grid points
 // (9 x 9 x 9: 1.42 points per cube; 4 x 4 x 16 cubes have 1.66) are staged once in LDS, energies and
-// orbital weights. Then, two ways:
-//  * the spline form (tetra_spline.h), nearly always: one lane per grid point forms the coefficients of the
-//    point's truncated powers from all tetrahedra of the tile around it and adds four entries per orbital to
-//    an LDS histogram of fourth differences (FP64 atomics, 8 lane-adds per clock and CU against 0.3 for FP32
-//    ones); four running sums down the histogram give the tile's DOS. The work per tile does not depend on
-//    the energy windows: 64^3 x 8 x 8 x 1000 took 0.32 ms with a loop over every tetrahedron's window and
-//    takes 0.167 ms; 24^3 x 8 x 8 x 4096, with windows of 75 energies, 0.04 ms. Bound by FP64 issue
-//    (about 560 instructions per point, 516 of them FP64) and the LDS (120 weight reads and 32 atomics per
-//    point of 8 orbitals) in about equal parts.
-//    Tetrahedra with nearly equal corner energies go through a queue, energy by energy.
-//  * the general form: one lane per cube, a five-comparator sort of the corner energies and a loop over each
-//    tetrahedron's energies. For the tile-bands that the spline form is not for: energy ranges beyond its
-//    histogram (thousands of energies), more than kQueue degenerate tetrahedra (a band without dispersion
-//    along an axis, a grid with a single point along one), weights that are not finite.
-//    The LDS histogram there holds 64-bit fixed-point integers (LDS FP32 atomics are slow): every
-//    contribution is non-negative (a corner weight is the section integral of a barycentric coordinate) and
-//    a tetrahedron's point DOS never exceeds 3 V_T/(V_G E41), so with bmax = max |b| of the tile, a bound
-//    B = sum 12 V bmax / E41 over the tetrahedra with a non-empty window bounds every bin's |sum| and fixes
-//    a power-of-two scale S with B*S <= 2^62 (two's complement, so signed weights work too). When the
-//    tile's weights are non-negative and its bound is not dominated by narrow tetrahedra (E41 < 2 de, whose
-//    spikes would make B loose), two orbitals share one 64-bit atomic as two 32-bit fields with
-//    B*S <= 2^30 (no carry between fields).
+// orbital weights. Then, into one LDS histogram (FP64 atomics, 8 lane-adds per clock and CU against 0.3 for FP32 ones):
+//  * the spline form (tetra_spline.h): one lane per grid point forms the coefficients of the point's truncated powers
+//    from all tetrahedra of the tile around it and adds four entries per orbital, fourth differences; four running
+//    sums down the histogram give the tile's DOS. The work per tile does not depend on the energy windows:
+//    64^3 x 8 x 8 x 1000 took 0.32 ms with a loop over every tetrahedron's window and takes 0.171 ms;
+//    24^3 x 8 x 8 x 4096, with windows of 75 energies, 0.04 ms. Bound by FP64 issue (about 560 instructions per point,
+//    516 of them FP64), the LDS (120 weight reads and 32 atomics per point of 8 orbitals) and the latencies of a
+//    unit's stages, of which two units per CU hide only part: each microsecond of the about 20 of a unit counts.
+//  * tetrahedra with nearly equal corner energies, energy by energy onto those sums (sum_tets): a few of generic bands,
+//    through a queue; hundreds to all of them where a lattice's symmetry or a band without dispersion along an axis
+//    makes energies equal. Four bands of 8 orbitals, 1000 energies, loop over every tetrahedron's window -> the form
+//    that threw the tile's spline form away for such a loop -> this: nearest neighbours on a simple cubic lattice 64^3
+//    0.28, 0.24, 0.18 ms, fcc 0.52, 0.34, 0.21 ms, layered 0.78, 0.92, 0.75 ms.
+//    So is everything in a tile-band whose energy range the histogram does not hold (thousands of energies) or with
+//    weights that are not finite.
 // One global float atomic per touched (energy, orbital) bin when the workgroup finishes.
 // Workgroups are assigned so that each XCD (eight per MI355X, each with its own L2) works through a
 // contiguous range of tiles of the same band, keeping shared halo points in one L2.
@@ -48,47 +41,24 @@ namespace tetra {
 
 namespace {
 
-// Words of the general form's LDS histogram.
-template <int NORB>
-constexpr int fwd_hist_words() { return NORB <= 8 ? 1280 : NORB == 16 ? 1344 : 2048; }
 // Common fixed point of the exact mode: with E the largest bound exponent of any workgroup (each
 // workgroup's bins sum to at most 2^E in magnitude) and L = ceil(log2(workgroups)), the total of any
 // bin is below 2^(E + L), so the scale 2^(62 - E - L) keeps every partial and total sum of the
 // 64-bit two's-complement accumulator in range.
 __device__ __forceinline__ int exact_scale_exp(int gexp, int lg_units) { return 62 - gexp - lg_units; }
 
-// Shared memory and body of the general form.
+// The bound of the exact mode for one work unit; every lane of the workgroup calls it: the exponent of
+// B = sum 12 V bmax / E41 over the tetrahedra with a possibly non-empty window into *gexp (atomicMax: independent of the
+// order). A tetrahedron's DOS never exceeds 3 V_T / (V_G E41), so no bin's |sum| over the unit exceeds B.
 template <int NORB>
-struct GeneralShared {
+struct BoundShared {
   float eps[NP];
-  float w[NP * NORB];
-  unsigned long long hist[fwd_hist_words<NORB>()];
-  float red[4 * NWMAX];
+  float red[3 * NWMAX];
 };
-
-// One work unit (tile, band) of the forward pass in the general form; every lane of the workgroup calls it.
-// MODE 0: DOS with per-workgroup scales, flushed with float atomics;
-// 1: only the workgroup's bound exponent, into *gexp (atomicMax: independent of the order);
-// 2: DOS with per-workgroup scales as in mode 0; each bin's exact per-workgroup sum is rounded once
-//    to the common fixed point fixed by *gexp and added to gacc with a 64-bit integer atomic. Both
-//    steps are independent of the order in which workgroups run, so the result is bitwise
-//    reproducible.
-template <int NORB, typename WT, int MODE>
-__device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, GeneralShared<NORB>& sh) {
-  constexpr int NPAIR = (NORB + 1) / 2;
-  // Histogram rows (one per orbital pair in the packed form, one per orbital in the wide form) have a
-  // fixed, odd stride in 64-bit words: the row offsets of a deposit are immediates, and the flush
-  // reads across rows without bank conflicts.
-  constexpr int HCAP = fwd_hist_words<NORB>();
-  constexpr int RSP = (HCAP / NPAIR - 1) | 1, RSW = (HCAP / NORB - 1) | 1;
-  float* const s_eps = sh.eps;
-  float* const s_w = sh.w;
-  unsigned long long* const s_hist = sh.hist;
-  float* const s_red = sh.red;
-
+template <int NORB, typename WT>
+__device__ __forceinline__ void bound_unit(const FwdArgs& a, int unit, BoundShared<NORB>& sh) {
   int band;
   const Tile tl = unit_tile(a, unit, band);
-  const int x0 = tl.x0, y0 = tl.y0, z0 = tl.z0;
   const int qy = tl.cy + 1, qz = tl.cz + 1, np = (tl.cx + 1) * qy * qz, ncubes = tl.cx * tl.cy * tl.cz;
   const int by_qz = small_inverse(qz), by_qy = small_inverse(qy);
   const int tid = threadIdx.x, NT = blockDim.x, NW = NT >> 6;
@@ -96,66 +66,42 @@ __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, General
   const float* eps_n = a.eps + (int64_t)band * nk;
   const WT* w_n = static_cast<const WT*>(a.w) + (int64_t)band * NORB * nk;
   const float wscale = a.w_scale ? a.w_scale[band] : 1.0f;
-
-  // Stage the tile's grid points (periodic wrap) and find their energy range.
-  float lmin = __builtin_huge_valf(), lmax = -__builtin_huge_valf(), lbmax = 0.0f, lbmin = 0.0f;
+  float lmin = __builtin_huge_valf(), lmax = -__builtin_huge_valf(), lbmax = 0.0f;
   for (int q = tid; q < np; q += NT) {
     const int r = small_div(q, by_qz), pz = q - r * qz, px = small_div(r, by_qy), py = r - px * qy;
-    const int p = px * PY + py * PZ + pz;
-    const int64_t k = ((int64_t)wrap(x0 + px, a.n1) * a.n2 + wrap(y0 + py, a.n2)) * a.n3 + wrap(z0 + pz, a.n3);
+    const int64_t k = ((int64_t)wrap(tl.x0 + px, a.n1) * a.n2 + wrap(tl.y0 + py, a.n2)) * a.n3 + wrap(tl.z0 + pz, a.n3);
     const float e = eps_n[k];
-    s_eps[p] = e;
+    sh.eps[px * PY + py * PZ + pz] = e;
     if (__builtin_isfinite(e)) {
       lmin = fminf(lmin, e);
       lmax = fmaxf(lmax, e);
     }
 #pragma unroll
-    for (int m = 0; m < NORB; ++m) {
-      const float b = weight_value(w_n[(int64_t)m * nk + k], wscale);
-      s_w[p * NORB + m] = b;
-      lbmax = fmaxf(lbmax, fabsf(b));
-      lbmin = fminf(lbmin, b);
-    }
+    for (int m = 0; m < NORB; ++m) lbmax = fmaxf(lbmax, fabsf(weight_value(w_n[(int64_t)m * nk + k], wscale)));
   }
   lmin = wave_min(lmin);
   lmax = wave_max(lmax);
   lbmax = wave_max(lbmax);
-  lbmin = wave_min(lbmin);
   if ((tid & 63) == 0) {
-    s_red[tid >> 6] = lmin;
-    s_red[NW + (tid >> 6)] = lmax;
-    s_red[2 * NW + (tid >> 6)] = lbmax;
-    s_red[3 * NW + (tid >> 6)] = lbmin;
+    sh.red[tid >> 6] = lmin;
+    sh.red[NW + (tid >> 6)] = lmax;
+    sh.red[2 * NW + (tid >> 6)] = lbmax;
   }
   __syncthreads();
-  float emin = s_red[0], emax = s_red[NW], bmax = s_red[2 * NW], bmin = s_red[3 * NW];
+  float emin = sh.red[0], emax = sh.red[NW], bmax = sh.red[2 * NW];
   for (int i = 1; i < NW; ++i) {
-    emin = fminf(emin, s_red[i]);
-    emax = fmaxf(emax, s_red[NW + i]);
-    bmax = fmaxf(bmax, s_red[2 * NW + i]);
-    bmin = fminf(bmin, s_red[3 * NW + i]);
+    emin = fminf(emin, sh.red[i]);
+    emax = fmaxf(emax, sh.red[NW + i]);
+    bmax = fmaxf(bmax, sh.red[2 * NW + i]);
   }
-  emin = uniform(emin);
-  emax = uniform(emax);
-  bmax = uniform(bmax);
-  bmin = uniform(bmin);
-  if (!(emin <= emax)) return;  // no finite energy in this tile-band (uniform across the block)
+  if (!(emin <= emax)) return;  // no finite energy
   int J0, J1;
   range_window(emin, emax, a.e0, a.inv_de, a.ne, J0, J1);
-
-  // This lane's cube; corner slot s sits at LDS point pbase + point_offset(s).
-  const bool valid = tid < ncubes;
-  int pbase = 0;
-  if (valid) {
-    const int r = tid / tl.cz, cz = tid - r * tl.cz, cx = r / tl.cy, cy = r - cx * tl.cy;
-    pbase = cx * PY + cy * PZ + cz;
-  }
-  auto point_offset = [](int s) { return (s & 1) * PY + ((s >> 1) & 1) * PZ + (s >> 2); };
-
-  // Bound on any bin's sum: sum over tetrahedra with a possibly non-empty window of 12 V bmax / E41.
-  float bound = 0.0f, narrow = 0.0f;
+  float bound = 0.0f;
   const float c12 = 12.0f * a.V * bmax;
-  if (valid) {
+  for_lanes(ncubes, [&](int c) {
+    const int r = c / tl.cz, iz = c - r * tl.cz, ix = r / tl.cy, iy = r - ix * tl.cy;
+    const float* fc = &sh.eps[ix * PY + iy * PZ + iz];
 #pragma unroll 1
     for (int t = 0; t < 6; ++t) {
       const uint32_t slots = tet_slots(t);
@@ -163,7 +109,8 @@ __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, General
       bool fin = true;
 #pragma unroll
       for (int l = 0; l < 4; ++l) {
-        const float e = s_eps[pbase + point_offset((slots >> (4 * l)) & 7)];
+        const int s = (slots >> (4 * l)) & 7;
+        const float e = fc[(s & 1) * PY + ((s >> 1) & 1) * PZ + (s >> 2)];
         fin = fin && __builtin_isfinite(e);
         lo = fminf(lo, e);
         hi = fmaxf(hi, e);
@@ -171,185 +118,19 @@ __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, General
       if (!fin || !(hi > lo)) continue;
       int jlo, jhi;
       energy_window(lo, hi, a.e0, a.inv_de, J0, J1, jlo, jhi);
-      if (jlo > jhi + 2) continue;
-      const float term = c12 * rcp(hi - lo);
-      bound += term;
-      if (hi - lo < 2.0f * a.de) narrow += term;
+      if (jlo <= jhi + 2) bound += c12 * rcp(hi - lo);
     }
-  }
+  });
   bound = wave_sum(fminf(bound, 1.0e37f));
-  narrow = wave_sum(fminf(narrow, 1.0e37f));
-  __syncthreads();  // every lane has read s_red
-  if ((tid & 63) == 0) {
-    s_red[tid >> 6] = bound;
-    s_red[NW + (tid >> 6)] = narrow;
-  }
+  __syncthreads();  // every lane has read sh.red
+  if ((tid & 63) == 0) sh.red[tid >> 6] = bound;
   __syncthreads();
-  float B = 0.0f, Bn = 0.0f;
-  for (int i = 0; i < NW; ++i) {
-    B += s_red[i];
-    Bn += s_red[NW + i];
-  }
-  B = uniform(B);
-  Bn = uniform(Bn);
-  if (!(B > 0.0f)) return;  // nothing to add (uniform across the block)
-  if (MODE == 1) {
-    if (tid == 0) {
-      int be;
-      frexpf(fminf(B, 3.0e38f), &be);
-      atomicMax(a.gexp, be);
-    }
-    return;
-  }
-  const bool packed = bmin >= 0.0f && Bn <= 0.5f * B;  // uniform across the block
-  const int rows = packed ? NPAIR : NORB;
-  const int RS = packed ? RSP : RSW;
-  // Copies: lane l adds into copy l % CP of a bin (each bin's copies are adjacent words), so the lanes
-  // of neighbouring cubes, which usually hit the same bins at the same time, do not serialise on one
-  // LDS address. As many copies (up to eight) as keep the tile-band's energy range in one pass.
-  const int span = uniform(J1 - J0 + 1);
-  const int cpl = span <= (RS >> 3) ? 3 : span <= (RS >> 2) ? 2 : span <= (RS >> 1) ? 1 : 0;  // log2 of the copy count
-  const int CP = 1 << cpl;
-  const int LC = RS >> cpl;  // bins per pass
-  int bexp;
-  frexpf(fminf(B, 3.0e38f), &bexp);  // B <= 2^bexp
-  const int sexp = uniform(min((packed ? 30 : 62) - bexp, 126));
-  const float S = ldexpf(1.0f, sexp);  // B * S <= 2^30 (packed) or 2^62
-  // exact mode: shift from this workgroup's fixed point to the common one (negative: to the right)
-  const int dshift = MODE == 2 ? exact_scale_exp(*a.gexp, a.lg_units) - sexp : 0;
-  // Fold the power-of-two scale into the staged weights (exact): every deposit is then an integer-valued
-  // float without a per-orbital multiply.
-  for (int q = tid; q < np; q += NT) {
-    const int r = small_div(q, by_qz), pz = q - r * qz, px = small_div(r, by_qy), py = r - px * qy;
-    float* w = &s_w[(px * PY + py * PZ + pz) * NORB];
-#pragma unroll
-    for (int m = 0; m < NORB; ++m) w[m] *= S;
-  }
-  __syncthreads();
-
-  for (int c0 = J0; c0 <= J1; c0 += LC) {
-    const int c1 = min(c0 + LC - 1, J1);
-    const int L = c1 - c0 + 1;
-    const int LW = L << cpl;  // words per row in this pass
-    // The lane index again, opaque: the addresses derived from it are formed in each pass instead of
-    // being kept live (in scratch) over the whole unit.
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    for (int q = tid; q < rows * LW; q += NT) {
-      const int r = q / LW;
-      s_hist[r * RS + (q - r * LW)] = 0ull;
-    }
-    __syncthreads();
-    if (valid) {
-#pragma unroll 1
-      for (int t = 0; t < 6; ++t) {
-        const uint32_t slots = tet_slots(t);
-        float e[4];
-        int pt[4];  // LDS point of each corner, carried through the sort
-#pragma unroll
-        for (int l = 0; l < 4; ++l) {
-          pt[l] = pbase + point_offset((slots >> (4 * l)) & 7);
-          e[l] = s_eps[pt[l]];
-        }
-        if (!finite4(e[0], e[1], e[2], e[3])) continue;
-        sort4(e, pt);
-        int jlo, jhi;
-        energy_window(e[0], e[3], a.e0, a.inv_de, c0, c1, jlo, jhi);
-        if (jlo > jhi + 2) continue;  // empty even after moving both ends by one
-        const TetSetup cs = tet_setup(e, a.e0, a.V);
-        tet_window(cs, a.de, c0, c1, jlo, jhi);
-        if (jlo > jhi) continue;
-        float bb[4][NORB];
-#pragma unroll
-        for (int l = 0; l < 4; ++l) {
-#pragma unroll
-          for (int m = 0; m < NORB; ++m) bb[l][m] = s_w[pt[l] * NORB + m];
-        }
-        // The window splits into the three energy cases at jA and jB.
-        int jA, jB;
-        case_split(cs, a.de, a.inv_de, jlo, jhi, jA, jB);
-        // Packed: two orbitals per 64-bit word as unsigned 32-bit fields; every term is non-negative
-        // (the weights are, and the corner weights are clamped at zero against rounding), so the
-        // truncating conversion of 0.5 + v rounds v to the nearest integer (halves up).
-        auto deposit = [&](int j, const float g[4]) {
-          unsigned long long* h = &s_hist[((j - c0) << cpl) + (tid & (CP - 1))];
-          if (packed) {
-#pragma unroll
-            for (int pr = 0; pr < NPAIR; ++pr) {
-              const int m0 = 2 * pr, m1 = 2 * pr + 1;
-              float v0 = __builtin_fmaf(g[0], bb[0][m0], 0.5f);
-              v0 = __builtin_fmaf(g[1], bb[1][m0], v0);
-              v0 = __builtin_fmaf(g[2], bb[2][m0], v0);
-              v0 = __builtin_fmaf(g[3], bb[3][m0], v0);
-              unsigned long long word = (unsigned long long)(unsigned)v0;
-              if (m1 < NORB) {
-                float v1 = __builtin_fmaf(g[0], bb[0][m1], 0.5f);
-                v1 = __builtin_fmaf(g[1], bb[1][m1], v1);
-                v1 = __builtin_fmaf(g[2], bb[2][m1], v1);
-                v1 = __builtin_fmaf(g[3], bb[3][m1], v1);
-                word |= (unsigned long long)(unsigned)v1 << 32;
-              }
-              atomicAdd(&h[pr * RSP], word);
-            }
-          } else {
-#pragma unroll
-            for (int m = 0; m < NORB; ++m) {
-              const float v = g[0] * bb[0][m] + g[1] * bb[1][m] + g[2] * bb[2][m] + g[3] * bb[3][m];
-              atomicAdd(&h[m * RSW], (unsigned long long)__float2ll_rn(v));
-            }
-          }
-        };
-        // One loop over the whole window: a wavefront runs as long as its longest window instead of
-        // the sum of its longest per-case ranges; each energy evaluates its own case's weights.
-        float coef[4][4];
-        if (jB > jA) corner_dos_B_coeffs(cs, a.V, coef);
-        for (int j = jlo; j <= jhi; ++j) {
-          float g[4];
-          if (j <= jA) {
-            corner_dos_A(cs, local_x(cs, j, a.de), g);
-            g[0] = fmaxf(g[0], 0.0f);  // g[1..3] are products of non-negative factors
-          } else if (j <= jB) {
-            corner_dos_B_poly(coef, local_z(cs, j, a.de), g);
-#pragma unroll
-            for (int l = 0; l < 4; ++l) g[l] = fmaxf(g[l], 0.0f);
-          } else {
-            corner_dos_C(cs, local_y(cs, j, a.de), g);
-            g[3] = fmaxf(g[3], 0.0f);
-          }
-          deposit(j, g);
-        }
-      }
-    }
-    __syncthreads();
-    for (int q = tid; q < L * NORB; q += NT) {
-      const int r = q / NORB, m = q - r * NORB;
-      const int row = packed ? (m >> 1) : m;
-      const unsigned long long* hw = &s_hist[row * RS + (r << cpl)];
-      if constexpr (MODE == 2) {
-        // exact sum of the copies in this workgroup's fixed point (|v| <= B S <= 2^62), then one
-        // rounding (halves up) to the common fixed point
-        long long v = 0;
-        for (int c = 0; c < CP; ++c) {
-          const unsigned long long w = hw[c];
-          v += packed ? (long long)(unsigned)((m & 1) ? (w >> 32) : (w & 0xffffffffull)) : (long long)w;
-        }
-        long long q;
-        if (dshift >= 0) q = (long long)((unsigned long long)v << dshift);
-        else if (dshift > -63) q = (v + (1ll << (-dshift - 1))) >> (-dshift);
-        else q = 0;  // |v| < 2^62 <= half a unit of the common fixed point
-        if (q != 0) atomicAdd(&a.gacc[(int64_t)(c0 + r) * NORB + m], (unsigned long long)q);
-      } else {
-        double sum = 0.0;
-        for (int c = 0; c < CP; ++c) {
-          const unsigned long long w = hw[c];
-          sum += packed ? (double)(unsigned)((m & 1) ? (w >> 32) : (w & 0xffffffffull)) : (double)(long long)w;
-        }
-        // the scale formed here rather than kept live over the passes (a register less there)
-        if (sum != 0.0) atomic_add_global(&a.dos[(int64_t)(c0 + r) * NORB + m], (float)ldexp(sum, -sexp));
-      }
-    }
-    __syncthreads();
-  }
+  float B = 0.0f;
+  for (int i = 0; i < NW; ++i) B += sh.red[i];
+  if (!(B > 0.0f) || tid != 0) return;
+  int be;
+  frexpf(fminf(B, 3.0e38f), &be);
+  atomicMax(a.gexp, be);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -358,7 +139,7 @@ __device__ __forceinline__ void general_unit(const FwdArgs& a, int unit, General
 template <int NORB>
 struct SplineFixed {
   double u[kKnotPad];  // knots: energies in grid steps
-  float f[NP];         // the energies, for the search for degenerate tetrahedra; infinite where not finite
+  float f[NP];         // the energies times `unit`, for the search for degenerate tetrahedra; infinite where not finite
   float wlo[kWeightPad];
   float w[NP * NORB];
   float whi[kWeightPad];
@@ -366,7 +147,7 @@ struct SplineFixed {
   unsigned short queue[kQueue];
   float red[3 * NWMAX];
   double dred[NWMAX];
-  int nq;
+  int nq, nout;  // left-out tetrahedra with finite corners, all of them
 };
 template <int NORB>
 constexpr int spline_words() { return (kLdsBytes - 64 - (int)sizeof(SplineFixed<NORB>)) / 8; }
@@ -375,20 +156,14 @@ struct SplineShared : SplineFixed<NORB> {
   double hist[spline_words<NORB>()];
 };
 
-template <int NORB>
-union FwdShared {
-  GeneralShared<NORB> general;
-  SplineShared<NORB> spline;
-};
-
-// The unit by the spline form; false (uniform across the workgroup) when the tile-band is not for it.
+// One work unit; every lane of the workgroup calls it.
 // MODE 0: FP64 sums, flushed with float atomics. MODE 2: 64-bit integers, so that nothing depends on the
 // order of the atomics: a first sweep over the points finds the largest entry, which fixes the scale.
 // MODE 3: the increments N(E_j) - N(E_{j-1}) of the number of states on the grid e0 + (j + joff) de
 // (everything below the grid at index 0) instead of the DOS: fifth differences of quartics, and the same
 // four running sums.
 template <int NORB, typename WT, int MODE>
-__device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineShared<NORB>& sh) {
+__device__ __forceinline__ void spline_unit(const FwdArgs& a, int unit, SplineShared<NORB>& sh) {
   using Acc = typename std::conditional<MODE == 2, long long, double>::type;
   constexpr bool INC = MODE == 3;
   constexpr int NE = INC ? 5 : 4;  // entries of a point
@@ -402,8 +177,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   const float* eps_n = a.eps + (int64_t)band * nk;
   const WT* w_n = static_cast<const WT*>(a.w) + (int64_t)band * NORB * nk;
   const float wscale = a.w_scale ? a.w_scale[band] : 1.0f;
-  const double e0 = a.e0, inv_de = a.inv_ded, joff = INC ? a.joff : 0.0;
-  if (nk >= (1ll << 29)) return false;  // byte offsets within a plane are 32-bit below
+  const double e0 = a.e0d, inv_de = a.inv_ded, joff = INC ? a.joff : 0.0;
   auto split = [&](int q, int& px, int& py, int& pz) {
     const int r = small_div(q, by_qz);
     pz = q - r * qz;
@@ -425,9 +199,9 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       int px, py, pz;
       split(q, px, py, pz);
       const uint32_t k = grid_index(px, py, pz);
-      ahead_e[i] = load_at(eps_n, k);
+      ahead_e[i] = eps_n[k];
 #pragma unroll
-      for (int m = 0; m < NORB; ++m) ahead_w[i][m] = load_at(w_n + (int64_t)m * nk, k);
+      for (int m = 0; m < NORB; ++m) ahead_w[i][m] = (w_n + (int64_t)m * nk)[k];
     }
   }
   for_lanes(kKnotPad, [&](int i) { sh.u[i] = kFarKnot; });
@@ -435,16 +209,16 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   for_lanes(NP, [&](int i) { sh.skip[i] = 0u; });
   if (np < NP)  // every word a neighbour offset can reach holds a finite value
     for_lanes(NP * NORB, [&](int i) { sh.w[i] = 0.0f; });
-  if (tid == 0) sh.nq = 0;
+  if (tid == 0) sh.nq = sh.nout = 0;
   __syncthreads();
   float lmin = __builtin_huge_valf(), lmax = -__builtin_huge_valf(), lbmax = 0.0f, lsum = 0.0f;
   auto stage = [&](int q, float e, auto&& weight) {
     int px, py, pz;
     split(q, px, py, pz);
     const int p = px * PY + py * PZ + pz;
-    const bool finite = __builtin_isfinite(e);
-    sh.f[p] = finite ? e : __builtin_huge_valf();
-    if (finite) {
+    const bool good = __builtin_isfinite(e);
+    sh.f[p] = good ? e * a.unit : __builtin_huge_valf();
+    if (good) {
       sh.u[kKnotMargin + px * SY + py * SZ + pz] = ((double)e - e0) * inv_de - joff;
       lmin = fminf(lmin, e);
       lmax = fmaxf(lmax, e);
@@ -466,7 +240,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       int px, py, pz;
       split(q, px, py, pz);
       const uint32_t k = grid_index(px, py, pz);
-      stage(q, load_at(eps_n, k), [&](int m) { return load_at(w_n + (int64_t)m * nk, k); });
+      stage(q, eps_n[k], [&](int m) { return (w_n + (int64_t)m * nk)[k]; });
     }
   }
   if (!(fabsf(lsum) < __builtin_huge_valf())) lbmax = __builtin_huge_valf();
@@ -487,14 +261,13 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
   }
   emin = uniform(emin);
   emax = uniform(emax);
-  if (!(emin <= emax)) return true;  // no finite energy
+  if (!(emin <= emax)) return;  // no finite energy
   const double umin = ((double)emin - e0) * inv_de - joff, umax = ((double)emax - e0) * inv_de - joff;
   auto index = [&](float e, bool above, double lo, double top) {  // INC
-    return energy_index(e, e0, (double)a.de, inv_de, joff, above, lo, top);
+    return energy_index(e, e0, a.ded, inv_de, joff, above, lo, top);
   };
   // above the energy grid (a flat tetrahedron on its last energy has all its states there)
-  if (INC ? index(emin, false, -1.0, (double)a.ne) > (double)(a.ne - 1) : !(umin < (double)(a.ne - 1))) return true;
-  if (!(uniform(bmax) < 3.0e38f)) return false;
+  if (INC ? index(emin, false, -1.0, a.ned) > (a.ned - 1.0) : !(umin < (a.ned - 1.0))) return;
   if (!(umax > 0.0)) {  // below it
     if (INC && a.shift == 0) {
       // every state counts at index 0: each finite tetrahedron gives V times its corners' weights
@@ -514,7 +287,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
               top = fmaxf(top, sh.f[q]);
               b += sh.w[m * NP + q];
             }
-            sum += top < __builtin_huge_valf() ? (double)b : 0.0;
+            sum += top < __builtin_huge_valf() && b == b ? (double)b : 0.0;
           }
         });
         if (sum != 0.0) unsafeAtomicAdd(&sh.hist[m], sum);
@@ -522,34 +295,36 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       __syncthreads();
       for_lanes(NORB, [&](int m) { atomic_add_global(&a.dos[m], (float)(sh.hist[m] * a.Vd)); });
     }
-    return true;
+    return;
   }
   // Rows of the sums: from the first grid energy at or above the lowest knot (below the grid's first
   // energy too) to the last one below the highest (the first at or above it for the increments).
-  const double rows_d = INC ? fmin(fmax(ceil(umax), index(emax, false, -1.0, (double)a.ne)), (double)(a.ne - 1)) + 1.0 - floor(umin)
-                            : fmin(ceil(umax), (double)a.ne) - floor(umin);
-  if (!(rows_d + NE + 2 <= (double)spline_words<NORB>())) return false;
-  const int base = uniform((int)floor(umin)), rows = uniform((int)rows_d);
-  const float J = (float)rows, limit = (MODE == 2 ? kDegenerateExact : a.degenerate) * J * J * J;
+  const double rows_d = INC ? fmin(fmax(ceil(umax), index(emax, false, -1.0, a.ned)), (a.ned - 1.0)) + 1.0 - floor(umin)
+                            : fmin(ceil(umax), a.ned) - floor(umin);
+  // Energy ranges beyond the histogram and weights that are not finite: every tetrahedron energy by energy.
+  const bool finite = uniform(bmax) < 3.0e38f;
+  const bool direct = !(rows_d + NE + 2 <= (double)spline_words<NORB>()) || !finite;
+  const int base = direct ? 0 : uniform((int)floor(umin)), rows = direct ? 0 : uniform((int)rows_d);
+  const float J = (float)rows, limit = (MODE == 2 ? a.degenerate_exact : a.degenerate) * J * J * J;
 
-  // Degenerate tetrahedra: their bits at their corner points, and a queue of those with finite corners.
+  // Degenerate tetrahedra: their bits at their corner points, and a queue of those with finite
+  // corners, as far as it goes.
   const int by_cz = small_inverse(cz), by_cy = small_inverse(cy);
-  for_lanes(ncubes, [&](int c) {
+  if (!direct) for_lanes(ncubes, [&](int c) {
     const int r = small_div(c, by_cz), iz = c - r * cz, ix = small_div(r, by_cy), iy = r - ix * cy;
     const float* fc = &sh.f[ix * PY + iy * PZ + iz];
     float f[8];
 #pragma unroll
     for (int s = 0; s < 8; ++s) f[s] = fc[(s & 1) * PY + ((s >> 1) & 1) * PZ + (s >> 2)];
-    uint32_t finite;
-    const uint32_t out = left_out(f, limit, finite, a.inv_de);
+    uint32_t whole;
+    const uint32_t out = left_out(f, limit, whole, a.width);
     if (out) {
+      atomicAdd(&sh.nout, __popc(out));
+      int at = atomicAdd(&sh.nq, __popc(whole));
 #pragma unroll
       for (int t = 0; t < 6; ++t) {
         if (!((out >> t) & 1u)) continue;
-        if ((finite >> t) & 1u) {
-          const int at = atomicAdd(&sh.nq, 1);
-          if (at < kQueue) sh.queue[at] = (unsigned short)(c * 6 + t);
-        }
+        if (((whole >> t) & 1u) && at < kQueue) sh.queue[at++] = (unsigned short)(c * 6 + t);
         const uint32_t slots = tet_slots(t);
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
@@ -561,13 +336,19 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     }
   });
   __syncthreads();
-  const int nq = uniform(sh.nq);
-  if (nq > kQueue) return false;
+  const int nq = direct ? 6 * ncubes : uniform(sh.nq);
+  const bool none = direct || uniform(sh.nout) == 6 * ncubes;  // nothing in the spline form
 
   // As many orbitals at a time as the histogram holds, then as many copies of it (a lane adds into copy
-  // lane mod copies: neighbouring points often share a bin).
-  const int RS = (rows + NE + 1) | 1;
-  int group = NORB;
+  // lane mod copies: neighbouring points often share a bin). Energy by energy alone: all orbitals, some energies at a time.
+  int group = NORB, RS = (rows + NE + 1) | 1;
+  int J0 = base, J1 = base + rows - 1;
+  if (direct) {
+    const double top = (a.ned - 1.0);
+    J0 = uniform((int)fmax(INC ? index(emin, false, 0.0, top) : floor(umin), 0.0));
+    J1 = uniform((int)fmin(INC ? index(emax, false, 0.0, top) : ceil(umax), top));
+    RS = (spline_words<NORB>() / NORB - 2) | 1;
+  }
   while ((RS * group | 1) > spline_words<NORB>()) group = (group + 1) / 2;
   const int plane = RS * group | 1;  // odd: the copies of a bin in different banks
   const int copies = histogram_copies(plane, spline_words<NORB>());
@@ -582,7 +363,10 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     const double* up = &sh.u[kKnotMargin + px * SY + py * SZ + pz];
     const double u0 = up[0];
     const double ju = ceil(u0);
-    if (!(ju - base < (double)rows)) return;  // above the last row (or not finite)
+    int b = base;  // opaque, so that no double of it is kept live over the whole unit
+    asm volatile("" : "+v"(b));
+    const double jr = ju - b;
+    if (!(jr < (double)rows)) return;  // above the last row (or not finite)
     double M[kNeighbours];
     const int p = px * PY + py * PZ + pz;
     knot_reciprocals(up, u0, M);
@@ -599,7 +383,7 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
       N[i] *= scale;
       n[i] *= scale * (INC ? (4.0 / 3.0) * T : T);
     }
-    const int row = (int)(ju - base);
+    const int row = (int)jr;
     auto orbital = [&](int m) {
       const float* w = sh.w + m * NP + p;
       const double bp = w[0];
@@ -614,115 +398,117 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
     for (int m = m0; m < m1; ++m) orbital(m);
   };
 
-  // Degenerate tetrahedra, energy by energy, 16 lanes each: the fourth differences 1, -4, 6, -4, 1 of the
-  // value at one energy. Called by the lanes in reverse order next to the points, of which the last waves
-  // have fewer.
-  auto degenerate = [&](int i16, int m0, int m1, double unit, auto&& add) {
-    const int i = i16 >> 4;
-    const int item = sh.queue[i], c = item / 6, t = item - 6 * c;
-    const int r = small_div(c, by_cz), iz = c - r * cz, ix = small_div(r, by_cy), iy = r - ix * cy;
-    const uint32_t slots = tet_slots(t);
-    float e[4];
-    int pt[4];
+  // The `count` tetrahedra of the queue energy by energy, or all that are left out (count: all there are), 2^lg lanes
+  // each: the energies [c0, c1] and orbitals [m0, m1) into rows from c0 on, lane i into plane i & planes. MODE 2: times
+  // 2^sexp.
+  // Next to each other in the tile are tetrahedra with the same energies (all along an axis without dispersion),
+  // and FP64 atomics to one address serialise: neighbouring lanes take tetrahedra an eighth of the queue apart, or of
+  // cubes of which no two in 64 lie in a line along an axis.
+  auto sum_tets = [&](int count, int lg, bool all, int m0, int m1, int c0, int c1, int planes, int sexp) {
+    constexpr int G = NORB < 8 ? NORB : 8;  // orbitals whose weights a lane holds
+    const double unit = MODE == 2 ? ldexp(1.0, sexp) : 1.0;
+    const int eighth = (count + 7) >> 3, area = tl.cx * cy, by_cx = small_inverse(tl.cx);
+    const float by_unit = step_unit(a.unit);
+    for_lanes((all ? count : 8 * eighth) << lg, [&](int i) {
+      const int k = i >> lg, sub = i & ((1 << lg) - 1);
+      int t, ix, iy, iz;
+      if (all) {
+        t = (k >= ncubes) + (k >= 2 * ncubes) + (k >= 3 * ncubes) + (k >= 4 * ncubes) + (k >= 5 * ncubes);
+        const int c = k - t * ncubes, z = small_div(small_div(c, by_cx), by_cy), r = c - z * area;
+        ix = small_div(r, by_cy);
+        iy = r - ix * cy;
+        iz = z + ix + iy;
+        iz -= small_div(iz, by_cz) * cz;
+        const uint32_t skip = sh.skip[ix * PY + (iy + 1) * PZ + iz];  // of corner 2, which all six have
+        if (!direct && !((skip >> ((0x14100c090502ull >> (8 * t)) & 31)) & 1u)) return;
+      } else {
+        const int q = (k & 7) * eighth + (k >> 3);
+        if (q >= count) return;
+        const int it = sh.queue[q], c = it / 6, r = small_div(c, by_cz);
+        t = it - 6 * c;
+        iz = c - r * cz;
+        ix = small_div(r, by_cy);
+        iy = r - ix * cy;
+      }
+      const uint32_t slots = tet_slots(t);
+      float e[4];
+      int pt[4];
 #pragma unroll
-    for (int l = 0; l < 4; ++l) {
-      const int s = (slots >> (4 * l)) & 7;
-      const int px = ix + (s & 1), py = iy + ((s >> 1) & 1), pz = iz + (s >> 2);
-      e[l] = eps_n[((int64_t)wrap(x0 + px, a.n1) * a.n2 + wrap(y0 + py, a.n2)) * a.n3 + wrap(z0 + pz, a.n3)];
-      pt[l] = px * PY + py * PZ + pz;
-    }
-    sort4(e, pt);
-    if (!INC && !(e[3] > e[0])) return;
-    auto put = [&](int j, double g0, double g1, double g2, double g3) {
+      for (int l = 0; l < 4; ++l) {
+        const int s = (slots >> (4 * l)) & 7;
+        pt[l] = (ix + (s & 1)) * PY + (iy + ((s >> 1) & 1)) * PZ + iz + (s >> 2);
+        e[l] = sh.f[pt[l]] * by_unit;
+      }
+      if (!finite4(e[0], e[1], e[2], e[3])) return;
+      sort4(e, pt);
+      if (!INC && !(e[3] > e[0])) return;
+      Acc* const h0 = hist + (i & planes) * plane - c0;
 #pragma unroll 1
-      for (int m = m0; m < m1; ++m) {
-        const float* w = sh.w + m * NP;
-        const double v = unit * (g0 * w[pt[0]] + g1 * w[pt[1]] + g2 * w[pt[2]] + g3 * w[pt[3]]);
-        Acc* h = &hist[(m - m0) * RS + j - base];
-        add(h, v, 1);
-        add(h + 1, v, -4);
-        add(h + 2, v, 6);
-        add(h + 3, v, -4);
-        add(h + 4, v, 1);
-      }
-    };
-    if constexpr (INC) {
-      const NosVolumes c = nos_volumes(e);
-      const int full = (int)index(e[3], false, base, (double)a.ne), js = min(full, base + rows - 1);
-      const int ja = min((int)index(e[0], true, base, (double)a.ne), js);
-      for (int j = ja + (i16 & 15); j <= js; j += 16) {
-        double w0[4] = {0.0, 0.0, 0.0, 0.0}, w1[4] = {1.0, 1.0, 1.0, 1.0};
-        if (j > ja) corner_nos(c, 1.0, e0 + (j - 1 + joff) * (double)a.de, w0);
-        if (j < full) corner_nos(c, 1.0, e0 + (j + joff) * (double)a.de, w1);
-        put(j, w1[0] - w0[0], w1[1] - w0[1], w1[2] - w0[2], w1[3] - w0[3]);
-      }
-    } else {
-      tet_energies(e, a, 0, a.ne - 1, i16 & 15, 16, [&](int j, const float g[4]) { put(j, g[0], g[1], g[2], g[3]); });
-    }
-  };
-
-  for (int m0 = 0; m0 < NORB; m0 += group) {
-    const int m1 = min(m0 + group, NORB), gm = m1 - m0;
-    for_lanes(copies * plane, [&](int i) { hist[i] = Acc(0); });
-    int sexp = 0;
-    if constexpr (MODE == 2) {
-      // Fixed point: entries below 2^51, sums of every bin (below 2^gexp) below 2^62.
-      double dmax = 0.0;
-      for_lanes(np, [&](int q) {
-        point(q, m0, m1, c4, [&](int, int, const double D[4]) {
-          dmax = fmax(dmax, fmax(fmax(fabs(D[0]), fabs(D[1])), fmax(fabs(D[2]), fabs(D[3]))));
-        });
-      });
-      for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o));
-      __syncthreads();
-      if ((tid & 63) == 0) sh.dred[tid >> 6] = dmax;
-      __syncthreads();
-      for (int i = 0; i < NW; ++i) dmax = fmax(dmax, sh.dred[i]);
-      int dexp;
-      frexp(fmax(dmax, 1.0e-290), &dexp);  // dmax < 2^dexp
-      sexp = min(51 - dexp, 62 - *a.gexp);
-    }
-    __syncthreads();
-    const double scale = MODE == 2 ? uniform(ldexp(c4, sexp)) : c4;
-    for_lanes(np, [&](int q) {
-      Acc* const mine = hist + (q & (copies - 1)) * plane;
-      point(q, m0, m1, scale, [&](int m, int row, const double D[NE]) {
-        Acc* h = &mine[(m - m0) * RS + row];
+      for (int mc = m0; mc < m1; mc += G) {
+        float wt[4][G];
 #pragma unroll
-        for (int i = 0; i < NE; ++i) {
-          if constexpr (MODE == 2) {
-            constexpr double magic = 6755399441055744.0;  // 1.5 * 2^52: the sum's low bits are the rounded value
-            const long long v = __double_as_longlong(D[i] + magic) - __double_as_longlong(magic);
-            atomicAdd(reinterpret_cast<unsigned long long*>(&h[i]), (unsigned long long)v);
-          } else {
-            unsafeAtomicAdd(&h[i], D[i]);
+        for (int m = 0; m < G; ++m) {
+          const int at = min(mc + m, m1 - 1);
+#pragma unroll
+          for (int l = 0; l < 4; ++l) wt[l][m] = sh.w[at * NP + pt[l]];
+          if (!finite) {  // a weight that is no number adds nothing
+            const float sum = (wt[0][m] + wt[1][m]) + (wt[2][m] + wt[3][m]);
+#pragma unroll
+            for (int l = 0; l < 4; ++l) wt[l][m] = sum == sum ? wt[l][m] : 0.0f;
           }
         }
-      });
+        auto put = [&](int j, const float g[4]) {
+          Acc* h = h0 + (mc - m0) * RS + j;
+#pragma unroll
+          for (int m = 0; m < G; ++m) {
+            if (mc + m >= m1) continue;
+            const float v = g[0] * wt[0][m] + g[1] * wt[1][m] + g[2] * wt[2][m] + g[3] * wt[3][m];
+            if constexpr (MODE == 2)
+              atomicAdd(reinterpret_cast<unsigned long long*>(h + m * RS), (unsigned long long)(long long)rint(unit * v));
+            else
+              unsafeAtomicAdd(h + m * RS, (double)v);
+          }
+        };
+        if constexpr (INC) {
+          // Nothing below the first increment (everything below the grid counts at its first energy), everything
+          // from the last one on; a lane takes energies in a row.
+          int lo = direct && c0 == 0 ? 0 : c0 - 1;  // opaque, as in `point`
+          asm volatile("" : "+v"(lo));
+          const int full = (int)index(e[3], false, lo, a.ned);
+          const int ja = min((int)index(e[0], true, lo, a.ned), full), ji = max(ja, c0), j1 = min(full, c1);
+          const int per = (j1 - ji + (1 << lg)) >> lg, j0 = ji + sub * per, last = min(j0 + per - 1, j1);
+          if (j0 > last) continue;
+          NosVolumes v = nos_volumes(e);
+          double prev[4] = {0.0, 0.0, 0.0, 0.0};
+          if (j0 > ja) corner_nos(v, a.Vd, e0 + (j0 - 1 + joff) * a.ded, prev);
+          for (int j = j0; j <= last; ++j) {
+            double cur[4] = {a.Vd, a.Vd, a.Vd, a.Vd};
+            float g[4];
+            asm volatile("" : "+v"(v.e[0]), "+v"(v.e[1]), "+v"(v.e[2]), "+v"(v.e[3]));  // no doubles of them kept live
+            if (j < full) corner_nos(v, a.Vd, e0 + (j + joff) * a.ded, cur);
+            schedule_fence();
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+              g[l] = (float)(cur[l] - prev[l]);
+              prev[l] = cur[l];
+            }
+            schedule_fence();
+            put(j, g);
+          }
+        } else {
+          tet_energies(e, a, max(c0, 0), c1, sub, 1 << lg, put);
+        }
+      }
     });
-    for_lanes(16 * nq, [&](int i16) {
-      degenerate(i16, m0, m1, MODE == 2 ? ldexp(1.0, sexp) : INC ? a.Vd : 1.0, [&](Acc* h, double v, int times) {
-        if constexpr (MODE == 2)
-          atomicAdd(reinterpret_cast<unsigned long long*>(h), (unsigned long long)(times * (long long)rint(v)));
-        else
-          unsafeAtomicAdd(h, v * times);
-      });
-    }, true);
-    __syncthreads();
-    running_sums(hist, gm, RS, plane, copies, rows);
-    __syncthreads();
-    const int lo = max(-base, 0);
-    if (INC && lo > 0 && a.shift == 0) {  // increments below the grid count at its first energy
-      for_lanes(lo * gm, [&](int i) {
-        const int m = i / lo;
-        unsafeAtomicAdd(&sh.hist[m * RS + lo], sh.hist[m * RS + i - m * lo]);
-      });
-      __syncthreads();
-    }
-    for_lanes((rows - lo) * gm, [&](int i) {
+  };
+  // The rows [lo, hi) of the histogram's `planes` + 1 planes, row r of energy row0 + r, into the result.
+  auto flush = [&](int lo, int hi, int row0, int m0, int gm, int planes, int sexp) {
+    asm volatile("" : "+s"(gm));  // its reciprocal is not kept over the groups of orbitals
+    for_lanes((hi - lo) * gm, [&](int i) {
       const int q = gm == NORB ? i / NORB : i / gm, r = lo + q, m = i - q * gm;
-      const Acc v = hist[m * RS + r];
-      const int64_t at = (int64_t)(base + r) * NORB + m0 + m;
+      Acc v = hist[m * RS + r];
+      for (int k = 1; k <= planes; ++k) v += hist[k * plane + m * RS + r];
+      const int64_t at = (int64_t)(row0 + r) * NORB + m0 + m;
       if constexpr (MODE == 2) {
         const int dshift = exact_scale_exp(*a.gexp, a.lg_units) - sexp;
         long long fixed;
@@ -731,24 +517,89 @@ __device__ __forceinline__ bool spline_unit(const FwdArgs& a, int unit, SplineSh
         else fixed = 0;
         if (fixed != 0) atomicAdd(&a.gacc[at], (unsigned long long)fixed);
       } else if constexpr (INC) {
-        if (v != 0.0 && base + r >= a.shift)
+        if (v != 0.0 && row0 + r >= a.shift)
           atomic_add_global(&a.dos[at - a.shift * NORB], (float)(v * a.out_scale));
       } else {
         if (v != 0.0) atomic_add_global(&a.dos[at], (float)v);
       }
     });
     __syncthreads();
+  };
+
+  const int lots = uniform(direct ? (J1 - J0 + RS) / RS : (NORB + group - 1) / group);
+  for (int lot = 0; lot < lots; ++lot) {
+    const int m0 = direct ? 0 : lot * group, m1 = min(m0 + group, NORB), gm = m1 - m0;
+    const int c0 = direct ? J0 + lot * RS : J0, c1 = direct ? min(c0 + RS - 1, J1) : J1;
+    int zero = 0;  // opaque, so that no register pair of it is kept
+    asm volatile("" : "+v"(zero));
+    for_lanes(copies * plane, [&](int i) { hist[i] = (Acc)zero; });
+    int sexp = 0;
+    if constexpr (MODE == 2) {
+      // Fixed point: entries below 2^51, sums of every bin (below 2^gexp) below 2^62.
+      sexp = 62 - *a.gexp;
+      if (!none) {
+        double dmax = 0.0;
+        for_lanes(np, [&](int q) {
+          point(q, m0, m1, c4, [&](int, int, const double D[4]) {
+            dmax = fmax(dmax, fmax(fmax(fabs(D[0]), fabs(D[1])), fmax(fabs(D[2]), fabs(D[3]))));
+          });
+        });
+        for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o));
+        __syncthreads();
+        if ((tid & 63) == 0) sh.dred[tid >> 6] = dmax;
+        __syncthreads();
+        for (int i = 0; i < NW; ++i) dmax = fmax(dmax, sh.dred[i]);
+        int dexp;
+        frexp(fmax(dmax, 1.0e-290), &dexp);  // dmax < 2^dexp
+        sexp = min(51 - dexp, sexp);
+      }
+      sexp = uniform(sexp);
+    }
+    __syncthreads();
+    const int spread = nq > kQueue / 8 ? copies - 1 : 0;  // planes for the sums energy by energy
+    if (!none) {
+      const double scale = MODE == 2 ? uniform(ldexp(c4, sexp)) : c4;
+      for_lanes(np, [&](int q) {
+        Acc* const mine = hist + (q & (copies - 1)) * plane;
+        point(q, m0, m1, scale, [&](int m, int row, const double D[NE]) {
+          Acc* h = &mine[(m - m0) * RS + row];
+#pragma unroll
+          for (int i = 0; i < NE; ++i) {
+            if constexpr (MODE == 2) {
+              constexpr double magic = 6755399441055744.0;  // 1.5 * 2^52: the sum's low bits are the rounded value
+              const long long v = __double_as_longlong(D[i] + magic) - __double_as_longlong(magic);
+              atomicAdd(reinterpret_cast<unsigned long long*>(&h[i]), (unsigned long long)v);
+            } else {
+              unsafeAtomicAdd(&h[i], D[i]);
+            }
+          }
+        });
+      });
+      __syncthreads();
+      running_sums(hist, gm, RS, plane, copies, rows, spread > 0);
+      __syncthreads();
+    }
+    if (nq > 0) {  // the tetrahedra left out, onto the sums
+      const bool all = direct || nq > kQueue;
+      const int count = all ? 6 * ncubes : nq;
+      int lg = all ? (c1 - c0 >= kLongRows) : 4;
+      while (!all && lg > 0 && (count << lg) > NT) --lg;
+      sum_tets(count, lg, all, m0, m1, c0, c1, spread, sexp);
+      __syncthreads();
+    }
+    const int lo = max(-c0, 0);
+    if (INC && lo > 0 && a.shift == 0) {  // increments below the grid count at its first energy
+#pragma unroll 1
+      for (int m = 0; m < gm; ++m)
+        for_lanes(lo, [&](int r) {
+          double v = 0.0;
+          for (int k = 0; k <= spread; ++k) v += sh.hist[k * plane + m * RS + r];
+          unsafeAtomicAdd(&sh.hist[m * RS + lo], v);
+        });
+      __syncthreads();
+    }
+    flush(lo, c1 - c0 + 1, c0, m0, gm, spread, sexp);
   }
-
-  return true;
-}
-
-// One work unit: the spline form, or the general one for the tile-bands that are not for it.
-template <int NORB, typename WT, int MODE>
-__device__ __forceinline__ void forward_unit(const FwdArgs& a, int unit, FwdShared<NORB>& sh) {
-  if (spline_unit<NORB, WT, MODE>(a, unit, sh.spline)) return;
-  __syncthreads();
-  general_unit<NORB, WT, MODE>(a, unit, sh.general);
 }
 
 template <int NORB, typename WT, int MODE>
@@ -758,11 +609,11 @@ __global__ __launch_bounds__(NTMAX, kWaves) void dos_forward_kernel(FwdArgs a) {
   const int unit = (b % NXCD) * a.per_xcd + b / NXCD;
   if (unit >= a.nunits) return;
   if constexpr (MODE == 1) {
-    __shared__ GeneralShared<NORB> sh;
-    general_unit<NORB, WT, 1>(a, unit, sh);
+    __shared__ BoundShared<NORB> sh;
+    bound_unit<NORB, WT>(a, unit, sh);
   } else {
-    __shared__ FwdShared<NORB> sh;
-    forward_unit<NORB, WT, MODE>(a, unit, sh);
+    __shared__ SplineShared<NORB> sh;
+    spline_unit<NORB, WT, MODE>(a, unit, sh);
   }
 }
 
@@ -772,7 +623,7 @@ __global__ __launch_bounds__(NTMAX, kWaves) void dos_forward_kernel(FwdArgs a) {
 
 template <int NORB, typename WT>
 __global__ __launch_bounds__(NTMAX, kWaves) void dos_batched_kernel(BatchArgs b) {
-  __shared__ FwdShared<NORB> sh;
+  __shared__ SplineShared<NORB> sh;
   const int blk = blockIdx.x;
   const int u = (blk % NXCD) * b.per_xcd + blk / NXCD;  // each XCD a contiguous range of units
   if (u >= b.total) return;
@@ -791,6 +642,9 @@ __global__ __launch_bounds__(NTMAX, kWaves) void dos_batched_kernel(BatchArgs b)
   a.e0 = it.e0;
   a.de = it.de;
   a.inv_de = 1.0f / it.de;
+  a.e0d = it.e0;
+  a.ded = it.de;
+  a.ned = it.ne;
   const double V = 1.0 / (24.0 * (double)it.n1 * it.n2 * it.n3);  // V_T / (4 V_G)
   a.V = (float)V;
   a.inv_ded = 1.0 / (double)it.de;
@@ -807,8 +661,10 @@ __global__ __launch_bounds__(NTMAX, kWaves) void dos_batched_kernel(BatchArgs b)
   a.by_t2 = it.by_t2;
   a.by_t3 = it.by_t3;
   a.ntiles = it.ntiles;
+  a.unit = step_unit(it.de);
+  a.width = it.de * a.unit;
   a.degenerate = it.degenerate;
-  forward_unit<NORB, WT, 0>(a, u - it.unit_begin, sh);
+  spline_unit<NORB, WT, 0>(a, u - it.unit_begin, sh);
 }
 
 // Zero every item's DOS (blockIdx.y = item).

@@ -45,6 +45,7 @@ hipError_t nos(const tetra_desc& d, const float* eps, const void* w, int wtype, 
   FwdArgs a = forward_args(d, eps, w, wtype, w_scale, out);
   if (binned) {  // increments between the midpoints E_j -+ de/2: ne + 1 grid indices, the first dropped
     a.ne = d.ne + 1;
+    a.ned = a.ne;
     a.joff = -0.5;
     a.shift = 1;
     a.out_scale = 1.0 / (double)d.de;

@@ -6,6 +6,7 @@
 #pragma once
 
 #include "tetra_device.h"
+#include "tetra_spline.h"
 
 namespace tetra {
 
@@ -71,19 +72,20 @@ __host__ __device__ __forceinline__ void corner_nos_C(const TetSetup& c, float V
 // three in the middle one, the whole less one in the third, and each of those carries a quarter of its
 // volume per vertex, shared out by the vertex's barycentric coordinates. V = V_T/(4 V_G).
 struct NosVolumes {
-  double e[4];
+  float e[4];
   double r21, r31, r41, r32, r42, r43;
 };
 __host__ __device__ __forceinline__ NosVolumes nos_volumes(const float e[4]) {
   NosVolumes c;
   for (int l = 0; l < 4; ++l) c.e[l] = e[l];
-  // Reciprocals of zero differences are infinite; the case that would use them is never selected.
-  c.r21 = 1.0 / (c.e[1] - c.e[0]);
-  c.r31 = 1.0 / (c.e[2] - c.e[0]);
-  c.r41 = 1.0 / (c.e[3] - c.e[0]);
-  c.r32 = 1.0 / (c.e[2] - c.e[1]);
-  c.r42 = 1.0 / (c.e[3] - c.e[1]);
-  c.r43 = 1.0 / (c.e[3] - c.e[2]);
+  // Reciprocals of zero differences are not finite; the case that would use them is never selected.
+  auto inverse = [&](int i, int j) { return rcp64((double)c.e[i] - (double)c.e[j]); };
+  c.r21 = inverse(1, 0);
+  c.r31 = inverse(2, 0);
+  c.r41 = inverse(3, 0);
+  c.r32 = inverse(2, 1);
+  c.r42 = inverse(3, 1);
+  c.r43 = inverse(3, 2);
   return c;
 }
 __host__ __device__ __forceinline__ void corner_nos(const NosVolumes& c, double V, double E, double w[4]) {
@@ -125,6 +127,7 @@ __host__ __device__ __forceinline__ double energy_index(float e, double e0, doub
   if (!(u > lo)) return lo;
   if (!(u < top)) return top;
   double j = ceil(u);
+  if (fabs(u - rint(u)) > 1.0e-6) return fmin(j, top);  // no rounding reaches the next index
   auto past = [&](double i) {
     const double r = __builtin_fma(-(i + joff), de, x);  // e - E_i
     return above ? r < 0.0 : r <= 0.0;

@@ -54,17 +54,28 @@ __host__ __device__ __forceinline__ double rcp64(double x) {
 #endif
 }
 
-// m^2 s min(1, E41) of a tetrahedron in grid steps from its corner energies, times `steps` that many steps, in two
-// sorted pairs (a0 <= a1, b0 <= b1). The differences are those of the energies as they are, exact for nearly equal
-// ones; in units or from an origin of their own they would be rounded at the scale of that. Zero for two equal finite corners, also beside infinite ones. (A tetrahedron narrower than a
-// grid step is held to an error relative to its states per step, not to its own density.)
-__host__ __device__ __forceinline__ float spline_gap(float a0, float a1, float b0, float b1, float steps = 1.0f) {
+// m^2 s min(width, E41) of a tetrahedron from its corner energies in units of which a grid step has `width`, in two
+// sorted pairs (a0 <= a1, b0 <= b1); the kernels' unit is a power of two (step_unit), so that the differences are those
+// of the energies as they are: exact for nearly equal ones, which in grid steps or from an origin of their own would be
+// rounded at the scale of that. Zero for two equal finite corners, also beside infinite ones. (A tetrahedron narrower
+// than a grid step is held to an error relative to its states per step, not to its own density.)
+__host__ __device__ __forceinline__ float spline_gap(float a0, float a1, float b0, float b1, float width = 1.0f) {
   const float e1 = fminf(a0, b0), e4 = fmaxf(a1, b1), c = fmaxf(a0, b0), d = fminf(a1, b1);
   const float e2 = fminf(c, d), e3 = fmaxf(c, d);
-  const float m = steps * fminf(fminf(e2 - e1, e3 - e2), e4 - e3);
-  return m * m * fminf(steps * fminf(e3 - e1, e4 - e2), 3.0e38f) * fminf(steps * (e4 - e1), 1.0f);
+  const float m = fminf(fminf(e2 - e1, e3 - e2), e4 - e3);
+  return m * m * fminf(fminf(e3 - e1, e4 - e2), 3.0e38f) * fminf(e4 - e1, width);
 }
-// A tetrahedron is left to the energy-by-energy sum where its spline_gap is below this times J^3: its terms
+// The power of two 2^k with which the grid step de times 2^k lies in [1, 2).
+__host__ __device__ __forceinline__ float step_unit(float de) {
+  union {
+    float f;
+    uint32_t u;
+  } x;
+  x.f = de;
+  x.u = (254u << 23) - (x.u & 0x7f800000u);
+  return x.f;
+}
+// A tetrahedron is left to the energy-by-energy sum where its spline_gap is below this times J^3 (width^4): its terms
 // would lose more than the share given of its own density at the far end of the sums. Plain sums end in
 // FP32 additions and their errors average over the tetrahedra; exact ones hold 51 bits.
 constexpr float kDegenerate = 2.2e-12f;       // 2e-4 of the density; 0.05 % of the tetrahedra of generic bands
@@ -75,7 +86,7 @@ constexpr float kDegenerateExact = 1.0e-10f;  // 4e-6; 0.4 %
 // f: the energies of the corners by slot, +infinity for one that is not finite. A tetrahedron with such a corner contributes
 // nothing; its far knot sees to that as long as no two of its other corners are equal, so it is left out as well
 // where they are (an edge next to the tile's end may belong to no other tetrahedron of the tile).
-__host__ __device__ __forceinline__ uint32_t left_out(const float f[8], float limit, uint32_t& finite, float steps = 1.0f) {
+__host__ __device__ __forceinline__ uint32_t left_out(const float f[8], float limit, uint32_t& finite, float width = 1.0f) {
   // Corners 2 and 5 belong to all six tetrahedra, the other two run around them.
   constexpr int I[6][2] = {{0, 1}, {1, 3}, {0, 4}, {3, 7}, {4, 6}, {6, 7}};
   const float d0 = fminf(f[2], f[5]), d1 = fmaxf(f[2], f[5]);
@@ -83,7 +94,7 @@ __host__ __device__ __forceinline__ uint32_t left_out(const float f[8], float li
 #pragma unroll
   for (int t = 0; t < 6; ++t) {
     const float a = f[I[t][0]], b = f[I[t][1]];
-    g[t] = spline_gap(d0, d1, fminf(a, b), fmaxf(a, b), steps);
+    g[t] = spline_gap(d0, d1, fminf(a, b), fmaxf(a, b), width);
   }
   uint32_t out = 0u;
   finite = 0u;

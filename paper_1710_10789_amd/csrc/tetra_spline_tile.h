@@ -19,7 +19,8 @@ constexpr int kWaves = 4;
 constexpr int kLdsBytes = 81920;
 constexpr int NXCD = 8;
 
-constexpr int kQueue = 256;                     // degenerate tetrahedra of a unit summed energy by energy
+constexpr int kQueue = 512;  // tetrahedra of a unit that are queued for the sum energy by energy
+constexpr int kLongRows = 256;  // energies from which on two lanes share a tetrahedron
 
 constexpr int SZ = PZ + 1, SY = PZ * SZ + SZ;     // strides of the knots, a far one at the end of every line and plane
 constexpr int kKnotMargin = SY + SZ + 1;        // the furthest neighbour offset
@@ -56,15 +57,15 @@ __device__ __forceinline__ Tile unit_tile(const FwdArgs& a, int unit, int& band)
   return t;
 }
 
-// q / d for q < 1024 and d <= 9 by a multiplication (inv = small_inverse(d)).
-__device__ __forceinline__ int small_inverse(int d) { return 65536 / d + 1; }
-__device__ __forceinline__ int small_div(int q, int inv) { return (q * inv) >> 16; }
-
-// p[k] with a 32-bit byte offset from a uniform pointer.
-template <typename T>
-__device__ __forceinline__ T load_at(const T* p, uint32_t k) {
-  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + (uint32_t)(k * (uint32_t)sizeof(T)));
+// q / d for q < 1024 and uniform d <= 9 by a multiplication (inv = small_inverse(d), 65536 / d + 1 without the vector
+// division that stands at the start of a unit otherwise).
+__device__ __forceinline__ int small_inverse(int d) {
+  int inv = 65537;
+#pragma unroll
+  for (int i = 2; i <= kSide + 1; ++i) inv = d == i ? 65536 / i + 1 : inv;
+  return inv;
 }
+__device__ __forceinline__ int small_div(int q, int inv) { return (q * inv) >> 16; }
 
 // 1 / (u_q - u0) of a knot's neighbours in the layout of the knots.
 __device__ __forceinline__ void knot_reciprocals(const double* up, double u0, double M[kNeighbours]) {
@@ -104,10 +105,13 @@ __device__ __forceinline__ int histogram_copies(int plane, int words) {
 }
 
 // Four running sums down each of the gm columns (RS words) of a histogram of `copies` planes, 128 rows at a
-// time; the result is in the first plane. A row more than there are is read and written at most.
+// time; the result is in the first plane, the others are cleared on demand. A row more than there are is read and written at most.
 template <typename Acc>
-__device__ __forceinline__ void running_sums(Acc* hist, int gm, int RS, int plane, int copies, int rows) {
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+__device__ __forceinline__ void running_sums(Acc* hist, int gm, int RS, int plane, int copies, int rows,
+                                             bool clear = false) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // nothing formed from it is kept live from one group of orbitals to the next
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int NW = blockDim.x >> 6;
   for (int m = wave; m < gm; m += NW) {
     Acc c[4] = {Acc(0), Acc(0), Acc(0), Acc(0)};
@@ -119,6 +123,7 @@ __device__ __forceinline__ void running_sums(Acc* hist, int gm, int RS, int plan
         for (int k = 0; k < copies; ++k) {
           v0 += hm[k * plane];
           v1 += hm[k * plane + 1];
+          if (clear) hm[k * plane] = hm[k * plane + 1] = Acc(0);
         }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {

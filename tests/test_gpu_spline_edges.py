@@ -171,3 +171,32 @@ def test_tile_ids_take_the_same_tiles(tile):
     args = (eps, w, grid, -0.02, float(np.float32(1.04 / (ne - 1))), ne)
     ref = tetra.dos_forward(*args, deterministic=True)
     assert torch.equal(ref, tetra.dos_forward(*args, deterministic=True, tile=tile))
+
+
+LATTICES = {  # bands with equal energies by symmetry, some of a tile's tetrahedra or all of them
+    "cubic": lambda x, y, z: np.cos(x) + np.cos(y) + np.cos(z),
+    "fcc": lambda x, y, z: np.cos(x) + np.cos(y) + np.cos(z) + np.cos(x - y) + np.cos(y - z) + np.cos(z - x),
+    "layers": lambda x, y, z: np.cos(x) + np.cos(y) + 0.3 * np.cos(x + y) + 0.0 * z,
+    "columns": lambda x, y, z: np.cos(x) + 0.0 * y + 0.0 * z,
+}
+
+
+@pytest.mark.parametrize("grid,norb,ne", [((16, 16, 16), 3, 60), ((9, 17, 8), 9, 700), ((10, 10, 6), 16, 3000),
+                                          ((8, 24, 1), 2, 90), ((1, 1, 50), 5, 300)])
+@pytest.mark.parametrize("name", sorted(LATTICES))
+@pytest.mark.parametrize("kind", KINDS)
+def test_equal_energies_by_symmetry(oracle_lib, kind, name, grid, norb, ne):
+    """More tetrahedra than the queue holds, all of them, in tiles shorter than eight cubes, with the orbitals in groups
+    and with energy ranges beyond the histogram."""
+    k = np.meshgrid(*[2 * np.pi * np.arange(n) / n for n in grid], indexing="ij")
+    e = LATTICES[name](*k).reshape(-1)
+    eps = np.stack([e, 0.7 * e + 0.2]).astype(np.float32)
+    w = np.random.default_rng(9).random((2, norb, e.size)).astype(np.float32)
+    lo, hi = float(eps.min()), float(eps.max())
+    de = float(np.float32(1.0371 * (hi - lo) / (ne - 1)))  # no energy of the band on a grid energy
+    print(f"[case] {kind} {name} {grid} {norb} {ne}", flush=True)
+    ref, got = _both(oracle_lib, kind, eps, w, grid, float(np.float32(lo - 0.0173 * (hi - lo))), de, ne, None)
+    assert np.isfinite(got).all()
+    err = dos_err(got, ref)
+    print(f"[case] err {err:.2e}", flush=True)
+    assert err <= 1e-5
