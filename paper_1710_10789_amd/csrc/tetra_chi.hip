@@ -653,7 +653,7 @@ hipError_t chi(const tetra_desc& d, int q1, int q2, int q3, float e_fermi, const
   const int grid = a.per_xcd * NXCD;
   a.ranges = static_cast<const float2*>(ranges_ws);
   ChiSplineArgs c;
-  c.f = forward_args(d, eps, w, wtype, w_scale, out);
+  c.f = forward_args(d, eps, w, wtype, w_scale, out, false);
   c.nb = d.nb;
   c.parts = parts(c.f.ntiles, 12288);
   c.q1 = a.q1;

@@ -27,9 +27,10 @@ __global__ void exact_init_kernel(int* gexp, unsigned long long* acc, int64_t n)
 }  // namespace
 
 constexpr int kSide = 8;  // largest tile side, in cubes
+constexpr int kCus = 256;
 
-FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale,
-                     float* dos) {
+FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
+                     bool alone) {
   FwdArgs a;
   a.eps = eps;
   a.w = w;
@@ -68,15 +69,20 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
   a.shift = 0;
   const int n[3] = {d.n1, d.n2, d.n3};
   // Tiles of 8 x 8 x 8 whatever shape the caller asks for: with the sides of the shapes the forward took 0.29 ms
-  // (8 x 8 x 4) to 0.63 ms (4 x 8 x 4) at 64^3 x 8 x 8 x 1000 against 0.17 ms.
+  // (8 x 8 x 4) to 0.63 ms (4 x 8 x 4) at 64^3 x 8 x 8 x 1000 against 0.17 ms. Where these leave half of the CUs or more
+  // without a workgroup, tiles of half or a quarter of that, at the same number of lanes: a unit's time is what counts
+  // there. 16^3 x 8 x 8 x 100 22 -> 18 us, four simple cubic bands 54 -> 23 us (42 us before the spline form).
+  int side[3] = {kSide, kSide, kSide};
+  auto tiles = [&](int i) { return (n[i] + side[i] - 1) / side[i]; };
+  for (int i = 0; alone && i < 2 && 2ll * tiles(0) * tiles(1) * tiles(2) * d.nb <= kCus; ++i) side[i] = kSide / 2;
   int t[3], s[3], r[3], lanes = 1;
   for (int i = 0; i < 3; ++i) {
-    t[i] = (n[i] + kSide - 1) / kSide;
+    t[i] = tiles(i);
     s[i] = n[i] / t[i];
     r[i] = n[i] % t[i];
     lanes *= s[i] + (r[i] > 0);
   }
-  a.lanes = std::max((lanes + 63) / 64 * 64, 256);  // small and flat tiles: more lanes than cubes for the rest
+  a.lanes = std::max((lanes + 63) / 64 * 64, side[0] < kSide ? 512 : 256);  // small tiles: more lanes than cubes
   a.t2 = t[1];
   a.t3 = t[2];
   a.s1 = s[0];
@@ -105,7 +111,7 @@ hipError_t fill_zero(float* p, int64_t n, hipStream_t s) {
 
 hipError_t forward(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
                    void* exact_scratch, hipStream_t s) {
-  FwdArgs a = forward_args(d, eps, w, wtype, w_scale, dos);
+  FwdArgs a = forward_args(d, eps, w, wtype, w_scale, dos, true);
   // exact_scratch (exact mode): 256 bytes holding the largest bound exponent, then ne*norb 64-bit sums
   a.gexp = exact_scratch ? static_cast<int*>(exact_scratch) : nullptr;
   a.gacc = exact_scratch ? reinterpret_cast<unsigned long long*>(static_cast<char*>(exact_scratch) + 256) : nullptr;
@@ -175,7 +181,7 @@ hipError_t batched(const tetra_item* items, int n, int wtype, hipStream_t s) {
       const tetra_desc& d = items[i].d;
       if (d.norb != norb) continue;
       BatchItem& it = b.it[b.n++];
-      const FwdArgs f = forward_args(d, items[i].eps, items[i].w, wtype, nullptr, items[i].dos);
+      const FwdArgs f = forward_args(d, items[i].eps, items[i].w, wtype, nullptr, items[i].dos, n == 1);
       it.eps = items[i].eps;
       it.w = items[i].w;
       it.w_scale = wtype == TETRA_W_F16 ? items[i].w_scale : nullptr;

@@ -72,8 +72,9 @@ struct BatchArgs {
 };
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments");
 
-// The arguments that do not depend on the kind of sum.
-FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos);
+// The arguments that do not depend on the kind of sum; alone: there are no other problems to fill the chip with.
+FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
+                     bool alone);
 
 // Defined per orbital count in tetra_forward_inst*.hip.
 template <int NORB>

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) void column_scan_kernel(float* p, int n, int n
 
 hipError_t nos(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* out,
                bool binned, hipStream_t s) {
-  FwdArgs a = forward_args(d, eps, w, wtype, w_scale, out);
+  FwdArgs a = forward_args(d, eps, w, wtype, w_scale, out, true);
   if (binned) {  // increments between the midpoints E_j -+ de/2: ne + 1 grid indices, the first dropped
     a.ne = d.ne + 1;
     a.ned = a.ne;
