@@ -10,8 +10,8 @@
 // are two sweeps over the points (a unit with both is rare: the signs held beside the masks of one sweep took
 // more registers than there are). A cube has a word for each: which of its six take no part (bits 0-5, for the
 // negative ones 8-13), whether any does (bit 6 or 14); a point forms its mask from the eight cubes around it.
-// Tiles with weights that are not finite, more degenerate tetrahedra than the queue holds or energy ranges
-// beyond the histogram: a lane per tetrahedron, energy by energy into the histogram, some energies at a time.
+// Degenerate tetrahedra go energy by energy onto the sums, as in the forward; with weights that are not finite or energy
+// ranges beyond the histogram all of them.
 //
 // 64^3 x 8 x 8 x 500 (9,830 pairs of a tile and two bands with something to add, 19 % of their tetrahedra left out):
 // 0.71 ms, of it 0.15 workgroups that find no pair, 0.14 differences and words, 0.18 weights (16 loads per point,
@@ -213,10 +213,10 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
   // Rows of the sums: from the first grid energy at or above the lowest knot to the last one below the highest.
   const double umin = ((double)dmin - e0) * inv_de, umax = ((double)dmax - e0) * inv_de;
   const double rows_d = fmin(ceil(umax), a.ned) - floor(umin);
-  bool direct = !(rows_d + 6.0 <= (double)chi_spline_words<NORB>());
-  const int base = direct ? 0 : uniform((int)floor(umin)), rows = direct ? 1 : uniform((int)rows_d);
+  const bool wide = !(rows_d + 6.0 <= (double)chi_spline_words<NORB>());
+  const int base = wide ? 0 : uniform((int)floor(umin)), rows = wide ? 1 : uniform((int)rows_d);
   const int first = uniform((int)fmin(fmax(floor(umin), 0.0), a.ned));  // energy by energy
-  const int last = uniform((int)fmin(ceil(umax), (a.ned - 1.0)));
+  const int last = uniform((int)fmin(ceil(umax), a.ned - 1.0));
   const float J = (float)rows, limit = a.degenerate * J * J * J;
 
   // The cube's word; degenerate tetrahedra into the queue.
@@ -236,7 +236,7 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
     }
     cube_word(tid) = (unsigned short)bits;
   }
-  // The weights. One that is not finite counts as too many degenerate tetrahedra: energy by energy.
+  // The weights, and whether one of them is not finite.
   {
     const WT* w_n = static_cast<const WT*>(a.w) + (int64_t)n * NORB * nk;
     const WT* w_p = static_cast<const WT*>(a.w) + (int64_t)n2 * NORB * nk;
@@ -259,79 +259,89 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
         sum += fabsf(W) * 0x1p-20f;
       }
     });
-    if (!(sum < 3.0e38f)) atomicAdd(&sh.nq, kQueue + 1);
+    if (!(sum < 3.0e38f)) atomicOr(&sh.signs, 4);
   }
   __syncthreads();
   const int nq = uniform(sh.nq), signs = uniform(sh.signs);
-  direct = direct || nq > kQueue;
+  const bool finite = !(signs & 4), direct = wide || !finite;  // direct: every tetrahedron energy by energy
 
-  // A tetrahedron's corners sorted by d, with their points.
-  auto corners = [&](int i, int t, float d[4], int pt[4]) {
-    int ix, iy, iz;
-    cube(i, ix, iy, iz);
-    const uint32_t slots = tet_slots(t);
-#pragma unroll
-    for (int l = 0; l < 4; ++l) {
-      const int s = (slots >> (4 * l)) & 7;
-      pt[l] = (ix + (s & 1)) * PY + (iy + ((s >> 1) & 1)) * PZ + iz + (s >> 2);
-      d[l] = sh.d[pt[l]];
-    }
-    sort4(d, pt);
-  };
-
-  if (direct) {
-    if (tid < ncubes) {
-      float dc[8];
-      uint32_t in, neg;
-      analyse(tid, dc, in, neg);
-      cube_word(tid) = (unsigned short)(in | neg << 8);
-    }
-    constexpr int chunk = chi_spline_words<NORB>() / NORB;
-    for (int c0 = first; c0 <= last; c0 += chunk) {
-      const int c1 = min(c0 + chunk - 1, last), L = c1 - c0 + 1;
-      __syncthreads();
-      for_lanes(chunk * NORB, [&](int i) { sh.hist[i] = 0.0; });
-      __syncthreads();
-      constexpr int G = NORB < 8 ? NORB : 8;  // orbitals whose weights a lane holds
-#pragma unroll 1
-      for (int m0 = 0; m0 < NORB; m0 += G)
-      for_lanes(ncubes * 6, [&](int i6) {
-        const int ic = i6 / 6, t = i6 - 6 * ic;
-        const uint32_t bits = (uint32_t)cube_word(ic) >> t;
-        if (!(bits & 1u)) return;
-        float d[4], wt[4][G];
-        int pt[4];
-        corners(ic, t, d, pt);
-        const float sign = (bits & 0x100u) ? -1.0f : 1.0f;
-#pragma unroll
-        for (int l = 0; l < 4; ++l)
-#pragma unroll
-          for (int m = 0; m < G; ++m) wt[l][m] = m0 + m < NORB ? sign * sh.w[(m0 + m) * NP + pt[l]] : 0.0f;
-        tet_energies(d, a, c0, c1, 0, 1, [&](int j, const float g[4]) {
-          double* h = &sh.hist[m0 * chunk + j - c0];
-#pragma unroll
-          for (int m = 0; m < G; ++m)
-            if (m0 + m < NORB) {
-              const float v = g[0] * wt[0][m] + g[1] * wt[1][m] + g[2] * wt[2][m] + g[3] * wt[3][m];
-              if (v == v) unsafeAtomicAdd(&h[m * chunk], (double)v);  // a weight that is no number adds nothing
-            }
-        });
-      });
-      __syncthreads();
-      for_lanes(L * NORB, [&](int i) {
-        const int r = i / NORB, m = i - r * NORB;
-        const double v = sh.hist[m * chunk + r];
-        if (v != 0.0) atomic_add_global(&a.dos[(int64_t)(c0 + r) * NORB + m], (float)v);
-      });
-    }
-    return;
+  int group = NORB, RS = (rows + 5) | 1, J0 = base, J1 = base + rows - 1;
+  if (direct) {  // all orbitals, some energies at a time
+    J0 = first;
+    J1 = last;
+    RS = (chi_spline_words<NORB>() / NORB - 2) | 1;
   }
-
-  const int RS = (rows + 5) | 1;
-  int group = NORB;
   while ((RS * group | 1) > chi_spline_words<NORB>()) group = (group + 1) / 2;
   const int plane = RS * group | 1;  // odd: the copies of a bin in different banks
   const int copies = histogram_copies(plane, chi_spline_words<NORB>());
+
+  // The `count` tetrahedra of the queue energy by energy, or all that take part and not in the spline form (count: all
+  // there are), 2^lg lanes each: the energies [c0, c1] and orbitals [m0, m1) into rows from c0 on, lane i into plane
+  // i & planes. Neighbouring lanes take tetrahedra that do not lie next to each other, as in the forward.
+  auto sum_tets = [&](int count, int lg, bool all, int m0, int m1, int c0, int c1, int planes) {
+    constexpr int G = NORB < 8 ? NORB : 8;  // orbitals whose weights a lane holds
+    const int eighth = (count + 7) >> 3, area = tl.cx * cy, by_cx = small_inverse(tl.cx);
+    for_lanes((all ? count : 8 * eighth) << lg, [&](int i) {
+      const int k = i >> lg, sub = i & ((1 << lg) - 1);
+      int t, ix, iy, iz;
+      if (all) {
+        t = (k >= ncubes) + (k >= 2 * ncubes) + (k >= 3 * ncubes) + (k >= 4 * ncubes) + (k >= 5 * ncubes);
+        const int q = k - t * ncubes, z = small_div(small_div(q, by_cx), by_cy), r = q - z * area;
+        ix = small_div(r, by_cy);
+        iy = r - ix * cy;
+        iz = z + ix + iy;
+        iz -= small_div(iz, by_cz) * cz;
+      } else {
+        const int q = (k & 7) * eighth + (k >> 3);
+        if (q >= count) return;
+        const int it = sh.queue[q], cb = it / 6;
+        t = it - 6 * cb;
+        cube(cb, ix, iy, iz);
+      }
+      const uint32_t slots = tet_slots(t);
+      float d[4];
+      int pt[4];
+      uint32_t side = 3u;
+#pragma unroll
+      for (int l = 0; l < 4; ++l) {
+        const int s = (slots >> (4 * l)) & 7;
+        pt[l] = (ix + (s & 1)) * PY + (iy + ((s >> 1) & 1)) * PZ + iz + (s >> 2);
+        d[l] = sh.d[pt[l]];
+        side &= sh.side[pt[l]];
+      }
+      // side 0: E_F cuts it or no transition (a corner without a finite energy has no side); both: flat
+      const uint32_t word = (uint32_t)sh.word[(ix + 1) * CY + (iy + 1) * CZ + iz + 1] >> t;
+      if (side == 0u || (!direct && !(word & ((side & 1u) ? 1u : 0x100u)))) return;
+      sort4(d, pt);
+      if (!(d[3] > d[0]) || !(d[3] > a.e0)) return;
+      const float sign = (side & 1u) ? 1.0f : -1.0f;
+      double* const h0 = sh.hist + (i & planes) * plane - c0;
+#pragma unroll 1
+      for (int mc = m0; mc < m1; mc += G) {
+        float wt[4][G];
+#pragma unroll
+        for (int m = 0; m < G; ++m) {
+          const int at = min(mc + m, m1 - 1);
+#pragma unroll
+          for (int l = 0; l < 4; ++l) wt[l][m] = sign * sh.w[at * NP + pt[l]];
+          if (!finite) {  // a weight that is no number adds nothing
+            const float sum = (wt[0][m] + wt[1][m]) + (wt[2][m] + wt[3][m]);
+#pragma unroll
+            for (int l = 0; l < 4; ++l) wt[l][m] = sum == sum ? wt[l][m] : 0.0f;
+          }
+        }
+        tet_energies(d, a, max(c0, 0), c1, sub, 1 << lg, [&](int j, const float g[4]) {
+          double* h = h0 + (mc - m0) * RS + j;
+#pragma unroll
+          for (int m = 0; m < G; ++m) {
+            if (mc + m >= m1) continue;
+            const float v = g[0] * wt[0][m] + g[1] * wt[1][m] + g[2] * wt[2][m] + g[3] * wt[3][m];
+            unsafeAtomicAdd(h + m * RS, (double)v);
+          }
+        });
+      }
+    });
+  };
 
   auto point = [&](int q, int sign, int m0, int m1, auto&& act) {
     int px, py, pz;
@@ -388,51 +398,47 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
     }
   };
 
-  for (int m0 = 0; m0 < NORB; m0 += group) {
-    const int m1 = min(m0 + group, NORB), gm = m1 - m0;
-    for_lanes(copies * plane, [&](int i) { sh.hist[i] = 0.0; });
+  const int lots = uniform(direct ? (J1 - J0 + RS) / RS : (NORB + group - 1) / group);
+  for (int lot = 0; lot < lots; ++lot) {
+    const int m0 = direct ? 0 : lot * group, m1 = min(m0 + group, NORB), gm = m1 - m0;
+    const int c0 = direct ? J0 + lot * RS : J0, c1 = direct ? min(c0 + RS - 1, J1) : J1;
+    int zero = 0;  // opaque, so that no register pair of it is kept
+    asm volatile("" : "+v"(zero));
+    for_lanes(copies * plane, [&](int i) { sh.hist[i] = (double)zero; });
     __syncthreads();
-    for (int sign = 0; sign < 2; ++sign) {
-      if (!((signs >> sign) & 1)) continue;
-      for_lanes(np, [&](int q) {
-        double* const mine = sh.hist + (q & (copies - 1)) * plane;
-        point(q, sign, m0, m1, [&](int m, int row, const double D[4]) {
-          double* h = &mine[(m - m0) * RS + row];
+    const int spread = nq > kQueue / 8 ? copies - 1 : 0;  // planes for the sums energy by energy
+    if (!direct) {
+      for (int sign = 0; sign < 2; ++sign) {
+        if (!((signs >> sign) & 1)) continue;
+        for_lanes(np, [&](int q) {
+          double* const mine = sh.hist + (q & (copies - 1)) * plane;
+          point(q, sign, m0, m1, [&](int m, int row, const double D[4]) {
+            double* h = &mine[(m - m0) * RS + row];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) unsafeAtomicAdd(&h[i], D[i]);
+            for (int i = 0; i < 4; ++i) unsafeAtomicAdd(&h[i], D[i]);
+          });
         });
-      });
+      }
+      __syncthreads();
+      running_sums(sh.hist, gm, RS, plane, copies, rows, spread > 0);
+      __syncthreads();
     }
-    // degenerate tetrahedra, 16 lanes each: the fourth differences of the value at one energy
-    for_lanes(16 * nq, [&](int i16) {
-      const int item = sh.queue[i16 >> 4], i = item / 6, t = item - 6 * i;
-      float d[4];
-      int pt[4];
-      corners(i, t, d, pt);
-      const bool minus = !(sh.side[pt[0]] & sh.side[pt[1]] & sh.side[pt[2]] & sh.side[pt[3]] & 1);
-      tet_energies(d, a, 0, a.ne - 1, i16 & 15, 16, [&](int j, const float g[4]) {
-#pragma unroll 1
-        for (int m = m0; m < m1; ++m) {
-          const float* w = sh.w + m * NP;
-          const double v = (double)g[0] * w[pt[0]] + (double)g[1] * w[pt[1]] + (double)g[2] * w[pt[2]] +
-                           (double)g[3] * w[pt[3]], x = minus ? -v : v;
-          double* h = &sh.hist[(m - m0) * RS + j - base];
-          unsafeAtomicAdd(h, x);
-          unsafeAtomicAdd(h + 1, -4.0 * x);
-          unsafeAtomicAdd(h + 2, 6.0 * x);
-          unsafeAtomicAdd(h + 3, -4.0 * x);
-          unsafeAtomicAdd(h + 4, x);
-        }
-      });
-    }, true);
-    __syncthreads();
-    running_sums(sh.hist, gm, RS, plane, copies, rows);
-    __syncthreads();
-    const int lo = max(-base, 0);
-    for_lanes((rows - lo) * gm, [&](int i) {
-      const int r0 = gm == NORB ? i / NORB : i / gm, r = lo + r0, m = i - r0 * gm;
-      const double v = sh.hist[m * RS + r];
-      if (v != 0.0) atomic_add_global(&a.dos[(int64_t)(base + r) * NORB + m0 + m], (float)v);
+    if (direct || nq > 0) {  // the tetrahedra left out, onto the sums
+      const bool all = direct || nq > kQueue;
+      const int count = all ? 6 * ncubes : nq;
+      int lg = all ? (c1 - c0 >= kLongRows) : 4;
+      while (!all && lg > 0 && (count << lg) > NT) --lg;
+      sum_tets(count, lg, all, m0, m1, c0, c1, spread);
+      __syncthreads();
+    }
+    const int lo = max(-c0, 0);
+    int gd = gm;
+    asm volatile("" : "+s"(gd));  // its reciprocal is not kept over the groups of orbitals
+    for_lanes((c1 - c0 + 1 - lo) * gm, [&](int i) {
+      const int r0 = gm == NORB ? i / NORB : i / gd, r = lo + r0, m = i - r0 * gm;
+      double v = sh.hist[m * RS + r];
+      for (int k = 1; k <= spread; ++k) v += sh.hist[k * plane + m * RS + r];
+      if (v != 0.0) atomic_add_global(&a.dos[(int64_t)(c0 + r) * NORB + m0 + m], (float)v);
     });
     __syncthreads();
   }

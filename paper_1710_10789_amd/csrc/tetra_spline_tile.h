@@ -19,7 +19,7 @@ constexpr int kWaves = 4;
 constexpr int kLdsBytes = 81920;
 constexpr int NXCD = 8;
 
-constexpr int kQueue = 512;  // tetrahedra of a unit that are queued for the sum energy by energy
+constexpr int kQueue = 512;     // tetrahedra of a unit that are queued for the sum energy by energy
 constexpr int kLongRows = 256;  // energies from which on two lanes share a tetrahedron
 
 constexpr int SZ = PZ + 1, SY = PZ * SZ + SZ;     // strides of the knots, a far one at the end of every line and plane

@@ -200,3 +200,27 @@ def test_equal_energies_by_symmetry(oracle_lib, kind, name, grid, norb, ne):
     err = dos_err(got, ref)
     print(f"[case] err {err:.2e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("grid,norb,ne", [((16, 16, 16), 3, 60), ((9, 17, 8), 9, 700), ((10, 10, 6), 16, 3000),
+                                          ((8, 24, 1), 2, 90), ((1, 1, 50), 5, 300)])
+@pytest.mark.parametrize("name", sorted(LATTICES))
+def test_susceptibility_of_equal_energies(oracle_lib, name, grid, norb, ne):
+    """The same for the differences of two bands, with transitions of both signs."""
+    import torch
+    import paper_1710_10789_amd as tetra
+
+    k = np.meshgrid(*[2 * np.pi * np.arange(n) / n for n in grid], indexing="ij")
+    e = LATTICES[name](*k).reshape(-1)
+    eps = np.stack([e, 0.7 * e + 0.2]).astype(np.float32)
+    w = np.random.default_rng(9).random((2, norb, e.size)).astype(np.float32)
+    wide = float(eps.max() - eps.min())
+    ef, q = float(np.float32(0.0613)), (grid[0] // 3, grid[1] // 4, grid[2] // 5)
+    de = float(np.float32(2.0371 * wide / (ne - 1)))
+    w0 = float(np.float32(-1.0119 * wide))
+    print(f"[case] {name} {grid} {norb} {ne}", flush=True)
+    ref, _ = oracle_lib.chi(eps, w, grid, q, ef, w0, de, ne)
+    got = tetra.chi_spectral(torch.from_numpy(eps).cuda(), torch.from_numpy(w).cuda(), grid, q, ef, w0, de, ne)
+    err = dos_err(got.double().cpu().numpy(), ref)
+    print(f"[case] err {err:.2e}", flush=True)
+    assert err <= 1e-5
