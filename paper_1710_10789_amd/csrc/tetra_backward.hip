@@ -26,6 +26,8 @@
 #include <algorithm>
 #include <type_traits>
 
+#include <cmath>
+
 #include "tetra_device.h"
 #include "tetra_faces.h"
 #include "tetra_internal.h"
@@ -471,13 +473,19 @@ hipError_t backward(const tetra_desc& d, const float* eps, const void* w, int wt
   a.t1 = (d.n1 + sh.x - 1) / sh.x;
   a.t2 = (d.n2 + sh.y - 1) / sh.y;
   a.t3 = (d.n3 + sh.z - 1) / sh.z;
-  // As many tiles as the shape gives, no longer than the grid needs: a shape that divides the grid as it is, otherwise
-  // fewer points and fewer waves with work. 24^3 x 8 x 8 x 300 (tiles of 12 along axis 3 instead of 16): 65 -> 60 us,
-  // 50 x 42 x 34 x 8 x 8 x 1000: 280 -> 266 us, 64 x 64 x 1 x 8 x 8 x 300: 134 -> 98 us. (The cubes of few tiles
-  // spread over all four waves instead of the first ones: 6 x 7 x 5 x 8 x 8 x 60 52 instead of 38 us.)
-  a.TX = (d.n1 + a.t1 - 1) / a.t1;
-  a.TY = (d.n2 + a.t2 - 1) / a.t2;
-  a.TZ = (d.n3 + a.t3 - 1) / a.t3;
+  // As many tiles as the shape gives, no longer than the grid needs where that saves points and waves: a grid thinner
+  // than the shape, or windows that are short next to what a unit spends on the rest, and units for all CUs. 24^3 x 8 x 8
+  // x 300 (tiles of 12 along axis 3 instead of 16) 69 -> 64 us, 50 x 42 x 34 x 8 x 8 x 1000 281 -> 267 us, 64 x 64 x 1 x 8
+  // x 8 x 300 145 -> 104 us. Otherwise the cubes stay spread over all four waves: shrunk tiles took 8 x 16 x 8 x 4 x 4 x
+  // 1000 from 130 to 143 us, 7 x 11 x 10 x 4 x 4 x 300 from 61 to 68 us, 27 x 23 x 34 x 16 x 16 x 3000 from 836 to 870 us.
+  const bool filled = (int64_t)a.t1 * a.t2 * a.t3 * d.nb > 256;
+  const bool short_windows = d.ne < 30.0 * std::cbrt((double)d.n1 * d.n2 * d.n3);
+  auto side = [&](int n, int shape, int tiles) {
+    return filled && (n < shape || short_windows) ? (n + tiles - 1) / tiles : shape;
+  };
+  a.TX = side(d.n1, sh.x, a.t1);
+  a.TY = side(d.n2, sh.y, a.t2);
+  a.TZ = side(d.n3, sh.z, a.t3);
   a.ntiles = a.t1 * a.t2 * a.t3;
   a.nunits = a.ntiles * d.nb;
   a.per_xcd = (a.nunits + NXCD - 1) / NXCD;
