@@ -63,6 +63,7 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
   const float width4 = a.width * a.width * a.width * a.width;
   a.degenerate = kDegenerate / (float)std::min(10.0, std::max(1.0, std::pow(points / 32768.0, 2.0 / 3.0))) * width4;
   a.degenerate_exact = kDegenerateExact * width4;
+  a.window = false;
   a.joff = 0.0;
   a.Vd = V;
   a.out_scale = 1.0;
@@ -102,6 +103,41 @@ FwdArgs forward_args(const tetra_desc& d, const float* eps, const void* w, int w
   return a;
 }
 
+namespace {
+
+// Whether the loop over every tetrahedron's window is the faster one. Its time grows with the energies of a window,
+// about ne / n of them on a grid of n points a side, the spline form's does not; the exact mode runs the spline form
+// twice and pays for its bound. The windows of an energy grid over a part of the bands are longer, so the lines lie
+// where the loop still is no slower over a third of them. Spline form -> loop, ms, whole bands (a third of them):
+//   64^3 x 8 x 8 x 32 0.163 -> 0.156 (0.166 -> 0.186), x 16 x 32 0.270 -> 0.211; 96^3 x 8 x 8 x 64 0.509 -> 0.490
+//   exact 64^3 x 8 x 8 x 64 0.335 -> 0.266, x 128 0.326 -> 0.291 (0.295 -> 0.315), x 256 0.315 -> 0.326;
+//   96^3 x 8 x 8 x 128 1.034 -> 0.862 (0.941 -> 0.862), 32^3 x 8 x 8 x 32 0.060 -> 0.050 (x 48 0.055 -> 0.069)
+// On a grid with one point along two axes every tetrahedron has equal energies: 1 x 1 x 4096 x 4 x 8 0.040 -> 0.025.
+bool few_energies(const tetra_desc& d, bool exact) {
+  if ((d.n1 == 1) + (d.n2 == 1) + (d.n3 == 1) > 1) return true;
+  const double face = std::cbrt((double)d.n1 * d.n2 * d.n3) * std::cbrt((double)d.n1 * d.n2 * d.n3);
+  return (exact ? (d.norb > 8 ? 55.0 : 40.0) : d.norb > 8 ? 110.0 : 200.0) * d.ne <= face;
+}
+
+// The arguments of tetra_window_kernels.h.
+FwdArgs window_args(FwdArgs a, const tetra_desc& d) {
+  const TileShape sh = tile_shape(0);
+  a.window = true;
+  a.s1 = sh.x;
+  a.s2 = sh.y;
+  a.s3 = sh.z;
+  a.t2 = (d.n2 + sh.y - 1) / sh.y;
+  a.t3 = (d.n3 + sh.z - 1) / sh.z;
+  a.ntiles = (d.n1 + sh.x - 1) / sh.x * a.t2 * a.t3;
+  a.nunits = a.ntiles * d.nb;
+  a.per_xcd = (a.nunits + NXCD - 1) / NXCD;
+  a.lg_units = 0;
+  while ((1ll << a.lg_units) < (long long)a.nunits) ++a.lg_units;
+  return a;
+}
+
+}  // namespace
+
 hipError_t fill_zero(float* p, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
@@ -112,6 +148,7 @@ hipError_t fill_zero(float* p, int64_t n, hipStream_t s) {
 hipError_t forward(const tetra_desc& d, const float* eps, const void* w, int wtype, const float* w_scale, float* dos,
                    void* exact_scratch, hipStream_t s) {
   FwdArgs a = forward_args(d, eps, w, wtype, w_scale, dos, true);
+  if (few_energies(d, exact_scratch != nullptr)) a = window_args(a, d);
   // exact_scratch (exact mode): 256 bytes holding the largest bound exponent, then ne*norb 64-bit sums
   a.gexp = exact_scratch ? static_cast<int*>(exact_scratch) : nullptr;
   a.gacc = exact_scratch ? reinterpret_cast<unsigned long long*>(static_cast<char*>(exact_scratch) + 256) : nullptr;

@@ -40,7 +40,8 @@ struct FwdArgs {
   int r1, r2, r3;
   FastDiv by_ntiles, by_t2, by_t3;
   int ntiles, nunits, per_xcd;
-  int lanes;  // workgroup size: a lane per cube of the largest tile, in whole waves
+  int lanes;    // workgroup size: a lane per cube of the largest tile, in whole waves
+  bool window;  // tetra_window_kernels.h with tiles of s1 x s2 x s3 cubes (the last ones partly outside the grid)
   // number of states: grid index j stands for e0 + (j + joff) de and goes to output row j - shift (rows below
   // 0 are dropped), times out_scale; Vd = V_T/(4 V_G)
   double joff, Vd, out_scale;

@@ -36,16 +36,11 @@
 #include "tetra_nos_device.h"
 #include "tetra_spline_tile.h"
 #include "tetra_weights.h"
+#include "tetra_window_kernels.h"
 
 namespace tetra {
 
 namespace {
-
-// Common fixed point of the exact mode: with E the largest bound exponent of any workgroup (each
-// workgroup's bins sum to at most 2^E in magnitude) and L = ceil(log2(workgroups)), the total of any
-// bin is below 2^(E + L), so the scale 2^(62 - E - L) keeps every partial and total sum of the
-// 64-bit two's-complement accumulator in range.
-__device__ __forceinline__ int exact_scale_exp(int gexp, int lg_units) { return 62 - gexp - lg_units; }
 
 // The bound of the exact mode for one work unit; every lane of the workgroup calls it: the exponent of
 // B = sum 12 V bmax / E41 over the tetrahedra with a possibly non-empty window into *gexp (atomicMax: independent of the
@@ -675,14 +670,21 @@ __global__ void batched_zero_kernel(BatchArgs b, int norb) {
     it.dos[i] = 0.0f;
 }
 
+template <int NORB, typename WT, int MODE>
+void launch_fwd_type(const FwdArgs& a, int grid, hipStream_t s) {
+  if (a.window)
+    hipLaunchKernelGGL((dos_window_kernel<NORB, WT, MODE>), dim3(grid), dim3(kTileCubes), 0, s, a);
+  else
+    hipLaunchKernelGGL((dos_forward_kernel<NORB, WT, MODE>), dim3(grid), dim3(a.lanes), 0, s, a);
+}
 template <int NORB, int MODE>
 hipError_t launch_fwd_mode(const FwdArgs& a, int grid, hipStream_t s) {
   if (a.wtype == TETRA_W_F16)
-    hipLaunchKernelGGL((dos_forward_kernel<NORB, _Float16, MODE>), dim3(grid), dim3(a.lanes), 0, s, a);
+    launch_fwd_type<NORB, _Float16, MODE>(a, grid, s);
   else if (a.wtype == TETRA_W_C32)
-    hipLaunchKernelGGL((dos_forward_kernel<NORB, float2, MODE>), dim3(grid), dim3(a.lanes), 0, s, a);
+    launch_fwd_type<NORB, float2, MODE>(a, grid, s);
   else
-    hipLaunchKernelGGL((dos_forward_kernel<NORB, float, MODE>), dim3(grid), dim3(a.lanes), 0, s, a);
+    launch_fwd_type<NORB, float, MODE>(a, grid, s);
   return hipGetLastError();
 }
 

@@ -224,3 +224,44 @@ def test_susceptibility_of_equal_energies(oracle_lib, name, grid, norb, ne):
     err = dos_err(got.double().cpu().numpy(), ref)
     print(f"[case] err {err:.2e}", flush=True)
     assert err <= 1e-5
+
+
+# grid, orbitals and energies on either side of the rule for calls with few of them (33^2 = 1089: up to 5 energies, 9
+# with more than 8 orbitals, in the exact mode 27 and 19), signed weights, a last tile of one cube
+FEW = [("dos", (33, 33, 33), 7, 5), ("dos", (33, 33, 33), 7, 6), ("dos", (36, 29, 33), 16, 9), ("dos", (1, 70, 1), 3, 500),
+       ("exact", (33, 33, 33), 7, 27), ("exact", (33, 33, 33), 7, 28), ("exact", (36, 29, 33), 16, 19),
+       ("exact", (36, 29, 33), 16, 20), ("exact", (1, 70, 1), 3, 500)]
+
+
+@pytest.mark.parametrize("kind,grid,norb,ne", FEW)
+@pytest.mark.parametrize("storage", ["f32", "signed", "f16", "c64"])
+def test_few_energies(oracle_lib, kind, grid, norb, ne, storage):
+    import torch
+    import paper_1710_10789_amd as tetra
+
+    rng = np.random.default_rng(ne)
+    nk = int(np.prod(grid))
+    k = np.meshgrid(*[2 * np.pi * np.arange(n) / n for n in grid], indexing="ij")
+    e = (np.cos(k[0] + 0.2) + 0.9 * np.cos(k[1] + 0.3 * k[0]) + 0.8 * np.cos(k[2] - k[1])).reshape(-1)
+    eps = np.stack([e, 0.6 * e + 0.3 * np.cos(k[2]).reshape(-1)]).astype(np.float32)
+    w = rng.random((2, norb, nk)).astype(np.float32) - np.float32(0.4 if storage == "signed" else 0.0)
+    scale = None
+    tw = torch.from_numpy(w).cuda()
+    if storage == "f16":
+        tw, scale = tetra.half_weights(tw)
+        w = (tw.float() * scale[:, None, None]).cpu().numpy()
+    elif storage == "c64":
+        tw = torch.polar(tw.sqrt(), tw)
+        w = (tw.real.double() ** 2 + tw.imag.double() ** 2).float().cpu().numpy()
+    lo, hi = float(eps.min()), float(eps.max())
+    e0, de = float(np.float32(lo + 0.01)), float(np.float32((hi - lo) / ne))
+    print(f"[case] {kind} {grid} {norb} {ne} {storage}", flush=True)
+    call = lambda: tetra.dos_forward(torch.from_numpy(eps).cuda(), tw, grid, e0, de, ne, w_scale=scale,  # noqa: E731
+                                     deterministic=kind == "exact")
+    got = call()
+    if kind == "exact":
+        assert torch.equal(got, call())
+    ref, _ = oracle_lib.dos(eps, w, grid, e0, de, ne)
+    err = dos_err(got.double().cpu().numpy(), ref)
+    print(f"[case] err {err:.2e}", flush=True)
+    assert err <= 1e-5
