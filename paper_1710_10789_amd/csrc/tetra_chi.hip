@@ -123,9 +123,9 @@ __global__ __launch_bounds__(NT) void chi_ranges_kernel(ChiArgs a) {
   }
 }
 
-// Waves per SIMD the kernel is held to: 88-128 VGPRs up to 8 orbitals, 133-168 above (20 and 40 bytes of scratch with
-// 15 and 16 orbitals, written and read with every lane active).
-constexpr int chi_waves(int norb) { return norb <= 8 ? 4 : 3; }
+// Waves per SIMD the kernel is held to: 88-128 VGPRs up to 8 orbitals, 133-168 up to 14, 183-189 above (at 3 waves 20 to
+// 44 bytes of scratch; 40^3 x 16 x 16 x 300, both passes, 1.67 and 1.64 ms at 3 and 2). No vector registers spilled.
+constexpr int chi_waves(int norb) { return norb <= 8 ? 4 : norb <= 14 ? 3 : 2; }
 
 // Whether E_F cuts one of the two bands: without, every region is a whole tetrahedron or empty.
 __device__ __forceinline__ bool crosses(float emin, float emax, float pmin, float pmax, float ef) {

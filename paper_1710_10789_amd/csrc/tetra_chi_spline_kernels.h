@@ -99,10 +99,12 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
     px = small_div(r, by_qy);
     py = r - px * qy;
   };
+  int n1 = a.n1, n2s = a.n2, n3 = a.n3;
+  asm volatile("" : "+s"(n1), "+s"(n2s), "+s"(n3));  // no copies in vector registers from one pair to the next
   auto grid_index = [&](int q, int s1, int s2, int s3) {
     int px, py, pz;
     split(q, px, py, pz);
-    return ((int64_t)wrap(x0 + px + s1, a.n1) * a.n2 + wrap(y0 + py + s2, a.n2)) * a.n3 + wrap(z0 + pz + s3, a.n3);
+    return ((int64_t)wrap(x0 + px + s1, n1) * n2s + wrap(y0 + py + s2, n2s)) * n3 + wrap(z0 + pz + s3, n3);
   };
 
   // The differences and the sides of E_F; the loads of a lane's first two points in flight while the LDS is
@@ -116,7 +118,9 @@ __device__ __forceinline__ void chi_spline_unit(const ChiSplineArgs& c, const Ti
       ahead_ep[i] = eps_p[grid_index(q, c.q1, c.q2, c.q3)];
     }
   }
-  for_lanes(kKnotPad, [&](int i) { sh.u[i] = kFarKnot; });
+  double far = kFarKnot;  // opaque: the constant is not kept from one pair to the next
+  asm volatile("" : "+v"(far));
+  for_lanes(kKnotPad, [&](int i) { sh.u[i] = far; });
   for_lanes(kWeightPad, [&](int i) { sh.wlo[i] = sh.whi[i] = 0.0f; });
   for_lanes(CZ * CY, [&](int i) { sh.word[i] = 0; });
   if (np < NP) {  // every word a neighbour offset can reach holds a finite value
