@@ -583,7 +583,7 @@ template <int NORB>
 hipError_t launch_chi(const ChiArgs& a, ChiSplineArgs& c, int wtype, int grid, hipStream_t s) {
   const int64_t units = (int64_t)c.f.ntiles * c.nb * c.parts;
   for (c.first = 0; c.first < units; c.first += c.nunits) {
-    c.nunits = (int)std::min<int64_t>(units - c.first, 1 << 30);
+    c.nunits = (int)std::min<int64_t>(units - c.first, 1 << 22);  // a launch holds fewer than 2^32 work items
     c.per_xcd = (c.nunits + NXCD - 1) / NXCD;
     const hipError_t e = launch_chi_spline<NORB>(c, s);
     if (e != hipSuccess) return e;
