@@ -40,3 +40,11 @@ def test_number_of_states_index_and_volumes(tmp_path, oracle_lib):
     rows = _run(tmp_path, oracle_lib, "nos_index_check")
     assert int(rows["index"][0]) == 40000 and int(rows["index"][1]) == 0
     assert float(rows["volumes"][0]) <= 1e-10
+
+
+def test_spline_form_at_the_smallest_limit(tmp_path, oracle_lib):
+    """A kept tetrahedron's loss goes with the inverse of the limit: 2e-3 of its own density at a tenth of it, and a
+    tenth of that in the sum over a block."""
+    rows = _run(tmp_path, oracle_lib, "spline_limit_check")
+    assert int(rows["block"][0]) == 60 and int(rows["block"][1]) > 100
+    assert float(rows["block"][2]) <= 2e-4 and float(rows["states"][0]) <= 2e-4
