@@ -219,8 +219,7 @@ tetra_status tetra_dos_backward_ws(const tetra_desc* d, const float* eps, const 
  * orbital m up to E_j per k-point (unit cell). Arguments as for tetra_dos_forward; nos is device
  * float [ne][norb], overwritten. flags: TETRA_TILE(shape) or 0 (TETRA_EXACT and TETRA_DETERMINISTIC
  * give TETRA_ERR_UNSUPPORTED). The kernels add the increments of each tetrahedron-band's weights
- * between neighbouring grid energies; the weights are evaluated in FP32, or in FP64 on the tiles
- * where a tetrahedron spans more than 64 energy steps (FP32 increments there would lose about
+ * between neighbouring grid energies, evaluated and added up in FP64 (FP32 increments would lose about
  * 1e-7 E41/de of their value to cancellation). Allocates nothing.
  */
 tetra_status tetra_nos_forward(const tetra_desc* d, const float* eps, const void* w, int wtype,

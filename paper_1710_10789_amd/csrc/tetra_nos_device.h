@@ -17,10 +17,11 @@ namespace tetra {
 //   middle case  w_l(z) = w_l(E2) + sum_k c_lk z^(k+1) / (k+1): the integral from E2 of the cubic
 //                dw_l/dE (the expansion written out at corner_dos_B_coeffs), with w_l(E2) the first
 //                case's value at x = E21.
-// Two precisions. The kernel adds increments w_l(E_j) - w_l(E_{j-1}); with bins much narrower than
-// the tetrahedron they are small differences of values up to V = V_T/(4 V_G), and FP32 evaluation
-// leaves them a relative error of about 1e-7 E41/de, FP64 about 1e-16 E41/de. The FP32 forms take
-// the float TetSetup, the FP64 ones a NosSetup.
+// The kernels add increments w_l(E_j) - w_l(E_{j-1}); with bins much narrower than the tetrahedron they are small
+// differences of values up to V = V_T/(4 V_G), and FP32 evaluation leaves them a relative error of about 1e-7 E41/de,
+// FP64 about 1e-16 E41/de. They use the FP64 volumes below (nos_volumes, corner_nos) and energy_index. The forms per
+// case, in FP32 (TetSetup) and FP64 (NosSetup), and the steps found from FP32 frames (shift_frames, step_window) are a
+// second writing of the same weights and steps that only checks on the host call.
 
 __host__ __device__ __forceinline__ void corner_nos_A(const TetSetup& c, float x, float w[4]) {
   const float t = c.kA * x * x * x;
@@ -137,7 +138,7 @@ __host__ __device__ __forceinline__ double energy_index(float e, double e0, doub
   return fmin(j, top);
 }
 
-// FP64 constants of one tetrahedron-band.
+// FP64 constants of one tetrahedron-band (checks on the host only).
 struct NosSetup {
   double x0, z0, y0;  // grid index 0 in the local frames: E_0 - E1, E_0 - E2, E4 - E_0
   double e21, e31, e41, e32, e42;

@@ -3,6 +3,7 @@
 For a problem class (GPU name, kernel, weight dtype, bands, orbitals, k-point bucket, energy-count
 bucket) every tile shape of ``TILE_SHAPES`` is timed on the current stream with HIP events (the best
 of two sweeps in opposite orders), and the fastest is kept in a JSON cache (``$TETRA_TUNE_CACHE``, default ``~/.cache/tetra_tune.json``).
+The forward works in tiles of 8x8x8 cubes whatever shape it is given: a saved choice of any age costs it nothing.
 Lookups of an untuned class fall back to the default shape 0.
 """
 from __future__ import annotations
