@@ -24,7 +24,7 @@
 // float atomic per touched (energy, orbital) bin at the end.
 //
 // 64^3 x 8 x 8 x 500: 1.72 ms when one kernel took both kinds of region (every tetrahedron's window energy by
-// energy), 1.37 ms now, 0.71 ms of it the spline pass and 0.65 ms this kernel's, bound by instruction issue: of that
+// energy), 1.40 ms now, 0.73 ms of it the spline pass and 0.65 ms this kernel's, bound by instruction issue: of that
 // about 0.13 ms staging and the search for regions, 0.06 ms weights, 0.17 ms listing the pieces and clearing and
 // flushing the histogram, 0.3 ms clipping and summing the pieces. Leaving the pieces in nine slots per region, two
 // or three of them filled, took 0.1 ms more, and workgroups for pairs that E_F cuts in neither band 0.15 ms.

@@ -14,8 +14,11 @@
 // ranges beyond the histogram all of them.
 //
 // 64^3 x 8 x 8 x 500 (9,830 pairs of a tile and two bands with something to add, 19 % of their tetrahedra left out):
-// 0.71 ms, of it 0.15 workgroups that find no pair, 0.14 differences and words, 0.18 weights (16 loads per point,
-// three times what the forward stages for its 8), 0.38 coefficients and contractions, 0.04 each deposits and sums.
+// 0.73 ms, of it 0.15 workgroups that find no pair, 0.14 differences and words, 0.18 weights (16 loads per point,
+// three times what the forward stages for its 8), 0.38 coefficients and contractions, 0.04 each deposits and sums. VALU
+// busy for 0.60 of the cycles, the LDS for 0.37. Four simple cubic bands x 8 orbitals, 64^3 x 1000, the whole call: 1.82 ms
+// with the loop over windows, 1.31 ms now (3.16 ms when tiles with many degenerate tetrahedra summed all of them energy
+// by energy); layered bands 6.56, 4.59 (15.3) ms.
 // No kernel here may spill vector registers (the compiler has placed such stores behind a loop's exit with no lane
 // active).
 #pragma once

@@ -16,7 +16,7 @@
 // Work decomposition and accumulation as in the forward kernels (tetra_forward_kernels.h, MODE 3): a grid point adds
 // the five fifth differences of its quartic per orbital, and four running sums give the tile's increments. The loop
 // over every tetrahedron's energies that it replaces took 0.45 ms for 64^3 x 8 x 8 x 1000 and, in FP64 where a
-// tetrahedron spanned more than 64 energies, 1.03 ms for 24^3 x 8 x 8 x 4096; now 0.196 and 0.043 ms.
+// tetrahedron spanned more than 64 energies, 1.03 ms for 24^3 x 8 x 8 x 4096; now 0.197 and 0.040 ms.
 // Tetrahedra with nearly equal corner energies are summed energy by energy: volumes in FP64 (an increment is a small
 // difference of values up to V), their differences with the weights in FP32. Layered bands, 64^3 x 4 x 8 x 1000:
 // 0.61 ms with the loop, 0.81 ms (3.2 ms with FP64 products into one plane of the histogram).
